@@ -61,7 +61,7 @@ void upload(ba_ctx* c, T** p, const std::vector<T>& h) {
 void free_ctx(ba_ctx* c) {
     if (!c) return;
     void* ptrs[] = {c->obs_cam, c->obs_pt, c->obs_row, c->obs_uv, c->chunk_q, c->chunk_ptr, c->long_ptr, c->cam_row,
-                    c->row_ptr, c->col_idx, c->off_blk, c->pair_ptr, c->trip, c->rowobs_ptr, c->rowobs,
+                    c->row_ptr, c->col_idx, c->trip, c->chip.brow, c->chip.cptr, c->chip.cols, c->rowobs_ptr, c->rowobs,
                     c->sf_ptr, c->sf_col, c->sf_src, c->Sf, c->Sf32, c->Su32, c->lo_ptr, c->lo_blk, c->unit_rng, c->unit_dst, c->lseg_blk, c->lseg_ptr, c->pblk, c->R, c->Jp, c->e, c->obs_rpos, c->ebar, c->ptL, c->blk, c->rhs, c->Minv,
                     c->Linv, c->Mlearn, c->dxc, c->dxp, c->part, c->part2, c->scal, c->flags, c->pcg.x, c->pcg.r[0],
                     c->pcg.r[1], c->pcg.z, c->pcg.q, c->pcg.d, c->pcg.t, c->pcg.u, c->pcg.tb, c->pcg.pA, c->pcg.pR, c->pcg.W, c->pcg.SW, c->pcg.Einv,
@@ -548,6 +548,13 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         lo_blk = std::move(tr_blk);
     }
     ph.mark("sf/lo lists");
+    ba::ChipPlan cp;
+    {
+        int n_cu = 0;
+        BA_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
+        ba::plan_chip(nr, sf_ptr.data(), sf_col.data(), n_cu, cp);
+    }
+    ph.mark("chip plan");
     std::vector<int32_t> row_ptr32(row_ptr.begin(), row_ptr.end());
     // device copies
     upload(c, &c->obs_cam, ocam);
@@ -558,8 +565,6 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     upload(c, &c->cam_row, cam_row);
     upload(c, &c->row_ptr, row_ptr32);
     upload(c, &c->col_idx, col_idx);
-    upload(c, &c->off_blk, off_blk);
-    upload(c, &c->pair_ptr, pair_ptr);
     upload(c, &c->trip, trip);
     upload(c, &c->unit_rng, unit_rng);
     upload(c, &c->unit_dst, unit_dst);
@@ -573,6 +578,13 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     upload(c, &c->sf_src, sf_src);
     upload(c, &c->lo_ptr, lo_ptr);
     upload(c, &c->lo_blk, lo_blk);
+    if (cp.G > 0) {
+        upload(c, &c->chip.brow, cp.brow);
+        upload(c, &c->chip.cptr, cp.cptr);
+        upload(c, &c->chip.cols, cp.cols);
+        c->chip.G = cp.G;
+        c->chip.NB = cp.NB;
+    }
     if (shared) upload(c, &c->img_cam, c->h_img_cam);
     BA_HIP_CHECK(hipStreamSynchronize(c->stream));
     ph.mark("uploads");

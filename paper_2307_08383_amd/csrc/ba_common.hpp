@@ -366,6 +366,17 @@ struct Csr {
     double* val = nullptr;         // [nnz]
 };
 
+// Plan of the solve that runs in one kernel (kernels_pcg_chip.hip): rows of
+// each workgroup and the ascending distinct columns of their blocks.
+struct ChipPlan {
+    int G = 0, NB = 0;             // workgroups (0: the system does not fit), blocks per lane group
+    std::vector<int32_t> brow, cptr, cols;
+};
+struct Chip {
+    int G = 0, NB = 0;
+    int32_t *brow = nullptr, *cptr = nullptr, *cols = nullptr;
+};
+
 }  // namespace ba
 
 struct ba_ctx {
@@ -395,7 +406,7 @@ struct ba_ctx {
     int32_t* cam_row = nullptr;        // [n_cams] RCS row or -1
     // pattern
     int32_t *row_ptr = nullptr, *col_idx = nullptr;
-    int32_t *off_blk = nullptr, *pair_ptr = nullptr, *trip = nullptr;
+    int32_t* trip = nullptr;
     int32_t *rowobs_ptr = nullptr, *rowobs = nullptr;
     // both triangles of the RCS by rows (upper blocks of the row, then the
     // transposed blocks of its column): pointer, column, source block << 1 |
@@ -445,6 +456,7 @@ struct ba_ctx {
     ba::Pcg pcg;
     ba::Fsai fs;
     ba::Csr csr;
+    ba::Chip chip;
     hipEvent_t ev[16] = {};
     hipStream_t capture_stream = nullptr;
     bool use_graphs = true;
@@ -509,6 +521,10 @@ void launch_update(ba_ctx* c, double* cams, double* pts, const double* dxc, cons
 // defl: deflate the similarity gauge (prepare_deflation first).
 ba_status run_pcg(ba_ctx* c, int mode, const double* Mblocks, int defl, double tol, int max_iter,
                   const double* x0, double* out, int* iters, double* relres);
+// the solve in one kernel, S held in registers (see kernels_pcg_chip.hip)
+void plan_chip(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P);
+bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, double tol, int max_iter, double* out);
+int64_t chip_slot_words();
 // gauge vectors of the last linearization's cameras, S W and (W^T S W)^-1
 void prepare_deflation(ba_ctx* c);
 // FSAI: index structure (host, once per context) and the factor of the

@@ -525,6 +525,13 @@ __global__ __launch_bounds__(BS) void k_pack_half(int64_t n_mem, const int32_t* 
 // PCG kernels
 // ---------------------------------------------------------------------------
 
+// what the set-up clears for the solve in one kernel (n_slot = 0: nothing)
+struct ChipWords {
+    double* vec[6];
+    double* slots;
+    int64_t n_slot;
+};
+
 // x = x_s (x0 or 0), r = rhs - q0 (q0 = S x0, or 0); deflated: x += W y,
 // r -= SW y with y = E^-1 W^T r_s.  With a block-diagonal preconditioner
 // also z = M^-1 r; partials of r^T z, r^T r, (SW)^T z (parity 0); the state.
@@ -535,7 +542,7 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
                                                  double* __restrict__ pR, int* __restrict__ state,
                                                  double* __restrict__ scal, int defl, const double* __restrict__ W,
                                                  const double* __restrict__ SW, const double* __restrict__ Einv,
-                                                 const double* __restrict__ pW, int n_part) {
+                                                 const double* __restrict__ pW, int n_part, ChipWords cw) {
     __shared__ double sr[RPB][9];
     __shared__ double sh[NP * WPB];
     double y[kW];
@@ -570,6 +577,11 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
             x[o] = xv;
             r[o] = rv;
             sr[lr][i] = rv;
+            if (cw.n_slot > 0) {   // q0 (one of these arrays) has been read
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+                    if (cw.vec[j]) cw.vec[j][o] = 0.0;
+            }
         }
         __syncthreads();
         if (act && M) {
@@ -592,7 +604,8 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
     block_totals<NP>(acc, t, sh);
     if (threadIdx.x == 0)
         for (int j = 0; j < NP; ++j) pR[(int64_t)NP * blockIdx.x + j] = t[j];
-    if (blockIdx.x == 0 && threadIdx.x == 0) { state[0] = 0; state[1] = 0; state[2] = BA_OK; state[3] = 0; scal[1] = -1.0; }
+    for (int64_t j = (int64_t)blockIdx.x * BS + threadIdx.x; j < cw.n_slot; j += (int64_t)gridDim.x * BS) cw.slots[j] = 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) { state[0] = 0; state[1] = 0; state[2] = BA_OK; state[3] = 0; state[4] = 0; scal[1] = -1.0; }
 }
 
 // plain y = S x
@@ -1314,17 +1327,38 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     Pcg& P = c->pcg;
     const int nr = c->n_rows, g = grid_of(nr);
     hipStream_t st = c->stream;
-    ensure_sf(c, false);
+    // FULL layout of a system that fits the chip: one kernel, straight from
+    // the upper blocks (2,000 cameras: 7.1 us an iteration against 16.8)
+    const bool chip = c->chip.G > 0 && !c->upper;
+    if (!chip || x0) ensure_sf(c, false);
     const double* q0 = nullptr;
     if (x0) {
         product_cur(c, x0, P.q, st);
         q0 = P.q;
     }
     if (defl) k_defl_Wr<<<g, BS, 0, st>>>(nr, c->rhs, q0, P.W, P.pW);
+    ChipWords cw{};
+    if (chip)
+        cw = {{P.u, P.q, P.d, P.r[1], P.tb, mode != 0 ? c->fs.tg : nullptr}, P.pE, chip_slot_words()};
     k_pcg_init<<<g, BS, 0, st>>>(nr, c->rhs, q0, x0, mode == 0 ? M : nullptr, P.x, P.r[0], P.z, P.pR, P.state, P.scal,
-                                 defl, P.W, P.SW, P.Einv, P.pW, g);
+                                 defl, P.W, P.SW, P.Einv, P.pW, g, cw);
     if (mode != 0) {
         launch_factor_init(c, g, defl, st);
+    }
+    if (chip) {
+        const bool launched = launch_chip(c, mode, M, defl, g, tol, max_iter, out);
+        if (launched) {
+            BA_HIP_CHECK(hipMemcpyAsync(c->h_flags + 4, P.state, 5 * sizeof(int), hipMemcpyDeviceToHost, st));
+            BA_HIP_CHECK(hipMemcpyAsync(c->h_scal + 8, P.scal, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+            BA_HIP_CHECK(hipStreamSynchronize(st));
+        }
+        if (launched && !c->h_flags[8]) {
+            *iters = c->h_flags[7];
+            *relres = c->h_scal[9];
+            return (ba_status)c->h_flags[6];
+        }
+        c->chip.G = 0;   // not all workgroups ran at once: this context solves with one kernel per phase
+        return run_pcg(c, mode, M, defl, tol, max_iter, x0, out, iters, relres);
     }
     launch_A<true>(c, g, tol, max_iter, defl, st);
     if (max_iter > 0) {
