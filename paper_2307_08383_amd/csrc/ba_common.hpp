@@ -52,10 +52,11 @@ __device__ __forceinline__ void rot_coeffs(double s, double& a, double& b, doubl
         bs = -1.0 / 24 + s * (2.0 / 720 + s * (-3.0 / 40320 + s * (4.0 / 3628800 + s * (-5.0 / 479001600 + s * (6.0 / 87178291200.0 + s * (-7.0 / 20922789888000.0))))));
     } else {
         const double th = sqrt(s), it = 1.0 / th, is = it * it;   // one division
-        double sn, cs;
-        sincos(th, &sn, &cs);
-        const double sh = sin(0.5 * th);
+        double sh, ch;
+        sincos(0.5 * th, &sh, &ch);   // the half angle gives all three
+        const double sn = 2.0 * sh * ch;
         const double omc = 2.0 * sh * sh;   // 1 - cos th without cancellation
+        const double cs = 1.0 - omc;
         a = sn * it;
         b = omc * is;
         as = (th * cs - sn) * (0.5 * is * it);
