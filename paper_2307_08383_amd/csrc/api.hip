@@ -68,7 +68,7 @@ void free_ctx(ba_ctx* c) {
                     c->pcg.pW, c->pcg.pE, c->lin_cams, c->pcg.state,
                     c->pcg.scal, c->fs.ptr, c->fs.J, c->fs.slot, c->fs.tptr, c->fs.tile, c->fs.brow,
                     c->fs.gu_ptr, c->fs.gu_col, c->fs.gu_pos, c->fs.gu_src, c->fs.gl_self, c->fs.tg, c->pcg.bm, c->fs.Gl, c->fs.Gu, c->fs.An, c->fs.G,
-                    c->fs.Gh, c->fs.hs, c->fs.Dn, c->tri_failed, c->img_cam, c->lin_params, c->lin_pts, c->csr.bptr, c->csr.slot_src, c->csr.slot_col, c->csr.slot_row, c->csr.rowptr, c->csr.col, c->csr.val};
+                    c->fs.Gh, c->fs.hs, c->fs.Dn, c->tri_failed, c->img_cam, c->slice_cam, c->slice_beg, c->slice_ptr, c->lin_params, c->lin_pts, c->csr.bptr, c->csr.slot_src, c->csr.slot_col, c->csr.slot_row, c->csr.rowptr, c->csr.col, c->csr.val};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (c->h_scal) (void)hipHostFree(c->h_scal);
@@ -466,8 +466,11 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         const int64_t groups = 256 * 16 * 4;
         const int64_t cap = 4 * std::max<int64_t>(8, steps / (4 * groups));
         int32_t n_p = 0;
-        for (int32_t sg = 0; sg < c->n_offseg; ++sg) {
+        // segments of more than kLongSeg chunks first
+        for (int pass = 0; pass < 2; ++pass) {
+          for (int32_t sg = 0; sg < c->n_offseg; ++sg) {
             const int32_t a = pair_ptr[sg], b = pair_ptr[sg + 1], w = clus[seg_row[sg]];
+            if ((b - a > ba::kLongSeg * cap) != (pass == 0)) continue;
             if (b - a <= cap) {
                 units.push_back({w, a, b, off_blk[sg]});
                 continue;
@@ -478,6 +481,8 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
             }
             lseg_blk.push_back(off_blk[sg]);
             lseg_ptr.push_back(n_p);
+          }
+          if (pass == 0) c->n_lseg_long = (int32_t)lseg_blk.size();
         }
         std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) {
             return x.win != y.win ? x.win < y.win : x.t1 - x.t0 > y.t1 - y.t0;
@@ -548,6 +553,22 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         lo_blk = std::move(tr_blk);
     }
     ph.mark("sf/lo lists");
+    // slices of the physical cameras' record lists (see ba_ctx): at most three
+    // a row in all, so that their sums fit the gauge vectors' array, which a
+    // shared-intrinsics context does not use
+    std::vector<int32_t> slice_cam, slice_beg, slice_ptr{0};
+    if (shared) {
+        c->node_len = (int32_t)std::max<int64_t>(1024, (n_rec + 2 * (int64_t)nr - 1) / (2 * (int64_t)nr));
+        for (int32_t k = 0; k < c->n_phys; ++k) {
+            const int32_t r = c->n_free + k;
+            for (int64_t i = rowobs_ptr[r]; i < rowobs_ptr[r + 1]; i += c->node_len) {
+                slice_cam.push_back(k);
+                slice_beg.push_back((int32_t)i);
+            }
+            slice_ptr.push_back((int32_t)slice_cam.size());
+        }
+        c->n_slice = (int32_t)slice_cam.size();
+    }
     ba::ChipPlan cp;
     {
         int n_cu = 0;
@@ -585,7 +606,12 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         c->chip.G = cp.G;
         c->chip.NB = cp.NB;
     }
-    if (shared) upload(c, &c->img_cam, c->h_img_cam);
+    if (shared) {
+        upload(c, &c->img_cam, c->h_img_cam);
+        upload(c, &c->slice_cam, slice_cam);
+        upload(c, &c->slice_beg, slice_beg);
+        upload(c, &c->slice_ptr, slice_ptr);
+    }
     BA_HIP_CHECK(hipStreamSynchronize(c->stream));
     ph.mark("uploads");
     c->h_row_ptr = std::move(row_ptr);

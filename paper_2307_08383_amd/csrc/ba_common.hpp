@@ -18,6 +18,7 @@ namespace ba {
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kMaxTrack = 64;      // observations per point handled by one wave (longer tracks: one workgroup)
 constexpr int kPcgBatch = 16;      // PCG iterations per enqueued batch (one graph)
+constexpr int kLongSeg = 24;       // chunks of a split pair segment summed by one thread per entry
 constexpr int kRec = 24;           // per-observation record: J_c (18), then K = J_p L^-T (6)
 
 // Durations of the phases of a host build (ba_create, the FSAI index
@@ -230,6 +231,43 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Sums over the wave of 64 values a lane: lane l receives the total of value
+// l.  Each step halves the values a lane holds (one half stays, the other goes
+// to a partner lane), 63 exchanges in all instead of six a value: lane ^ 32
+// and lane ^ 16 by register swaps, then the mirrored lane within 16 and within
+// 8 and lanes ^ 2, ^ 1 (DPP).  The diagonal stage of 16 rows 16.3 -> 8.6 us, of
+// 2,000 rows 95 -> 90, against wave_sum of each value.
+template <int CTRL, int H>
+__device__ __forceinline__ void halve_dpp(double* v, bool up) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const double keep = up ? v[i + H] : v[i], send = up ? v[i] : v[i + H];
+        v[i] = keep + dpp_mov<CTRL>(send);
+    }
+}
+template <int H, typename Swap>
+__device__ __forceinline__ void halve_swap(double* v, Swap&& swap) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const unsigned long long a = __builtin_bit_cast(unsigned long long, v[i]);
+        const unsigned long long b = __builtin_bit_cast(unsigned long long, v[i + H]);
+        const auto lo = swap((unsigned)a, (unsigned)b);
+        const auto hi = swap((unsigned)(a >> 32), (unsigned)(b >> 32));
+        v[i] = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+               __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+    }
+}
+__device__ __forceinline__ double wave_sums64(double (&v)[64]) {
+    const int lane = threadIdx.x % kWave;
+    halve_swap<32>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); });
+    halve_swap<16>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); });
+    halve_dpp<0x140, 8>(v, lane & 8);
+    halve_dpp<0x141, 4>(v, lane & 4);
+    halve_dpp<0x4E, 2>(v, lane & 2);
+    halve_dpp<0xB1, 1>(v, lane & 1);
+    return v[0];
+}
+
 // Track of a lane of a wave that holds a chunk of whole tracks (lane i holds
 // the chunk's observation i, i < len; a track's observations are adjacent):
 // the lane of the track's first observation, the track length and the
@@ -291,6 +329,47 @@ __device__ __forceinline__ void block_reduce(double* v, double (*sh)[NW]) {
         v[m] = t;
     }
     __syncthreads();
+}
+
+// Cholesky S = L L^T of a 9x9 block and Li = L^-1 (lower triangle, zero above)
+// by the lanes of one wave, S and Li in LDS, L scratch of the same size; false
+// (in every lane) if a pivot was not positive, which then counts as 1.  Lane
+// l < 45 holds element (r, c) of the lower triangle, l = r (r + 1) / 2 + c;
+// the inverse takes a lane per column.  (One lane did all of it: 16 rows took
+// the diagonal stage 18.9 us, 16.3 with the wave.)
+__device__ __forceinline__ bool wave_factor9(const double* S, double* L, double* Li, int lane) {
+    int r = 0;
+    while (r < 8 && (r + 1) * (r + 2) / 2 <= lane) ++r;
+    const int c = lane - r * (r + 1) / 2;
+    const bool act = lane < 45;
+    double v = act ? S[r * 9 + c] : 0.0;
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        double d = __shfl(v, k * (k + 3) / 2, kWave);
+        if (!(d > 0.0)) { ok = false; d = 1.0; }
+        const double s = sqrt(d);
+        if (act && c == k) v = r == k ? s : v / s;
+        const bool upd = act && c > k;
+        const double x = __shfl(v, upd ? r * (r + 1) / 2 + k : 0, kWave);
+        const double y = __shfl(v, upd ? c * (c + 1) / 2 + k : 0, kWave);
+        if (upd) v -= x * y;
+    }
+    if (act) L[r * 9 + c] = v;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 9) {
+        double x[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            double t = i == lane ? 1.0 : 0.0;
+#pragma unroll
+            for (int q = 0; q < i; ++q) t -= L[i * 9 + q] * x[q];   // x[q] = 0 above the column's diagonal
+            x[i] = i < lane ? 0.0 : t / L[i * 9 + i];
+            Li[i * 9 + lane] = x[i];
+        }
+    }
+    return ok;
 }
 
 // ---------------------------------------------------------------------------
@@ -436,7 +515,8 @@ struct ba_ctx {
     // split segment); split segment l sums partial blocks
     // [lseg_ptr[l], lseg_ptr[l+1]) into block lseg_blk[l].  Waves (4 units
     // each) [xcd_wv[x], xcd_wv[x+1]) run on XCD x.
-    int32_t n_unit = 0, n_lseg = 0, n_pblk = 0;
+    // the first n_lseg_long split segments have more than kLongSeg chunks
+    int32_t n_unit = 0, n_lseg = 0, n_lseg_long = 0, n_pblk = 0;
     int32_t xcd_wv[9] = {0};
     int32_t *unit_rng = nullptr, *unit_dst = nullptr, *lseg_blk = nullptr, *lseg_ptr = nullptr;
     double* pblk = nullptr;            // [n_pblk][81]
@@ -482,6 +562,11 @@ struct ba_ctx {
     std::vector<int32_t> h_img_cam;
     int32_t* img_cam = nullptr;
     double *lin_params = nullptr, *lin_pts = nullptr;   // parameters of the last linearization
+    // slices of the physical cameras' record lists (a camera's records are
+    // summed by several workgroups): camera of each slice, its first record,
+    // the slices of each camera; up to node_len records each
+    int32_t n_slice = 0, node_len = 0;
+    int32_t *slice_cam = nullptr, *slice_beg = nullptr, *slice_ptr = nullptr;
     bool have_lin = false, have_rcs = false, learned_ready = false;
     // Jp holds J_p of the current linearization (k_linearize writes it; the
     // fused linearize + point stage does not, and J_p = K L^T is formed from

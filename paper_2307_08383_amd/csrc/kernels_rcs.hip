@@ -445,38 +445,71 @@ __global__ __launch_bounds__(BS) void k_pair_sum(int n_lseg, const int32_t* __re
     blk[(int64_t)lseg_blk[l] * 81 + e] = v;
 }
 
+// The same for the segments of many chunks (a physical camera's own block, the
+// pairs of a landmark that most images see): a workgroup per segment, 12
+// groups of 81 threads each summing a contiguous part of its chunks in order,
+// then the groups in order.  With one thread walking all chunks the stage of
+// an 80-image block with 4 physical cameras took 303 us in it, 15 now.
+constexpr int kSumG = 12;
+__global__ __launch_bounds__(1024) void k_pair_sum_long(const int32_t* __restrict__ lseg_blk,
+                                                        const int32_t* __restrict__ lseg_ptr,
+                                                        const double* __restrict__ pblk, double* __restrict__ blk) {
+    __shared__ double sh[kSumG][81];
+    const int l = blockIdx.x, g = threadIdx.x / 81, e = threadIdx.x % 81;
+    const int p0 = lseg_ptr[l], n = lseg_ptr[l + 1] - p0, per = (n + kSumG - 1) / kSumG;
+    if (g < kSumG) {
+        const int a = p0 + min(n, g * per), b = p0 + min(n, (g + 1) * per);
+        double v = 0.0;
+        for (int p = a; p < b; p += 8) {
+            double t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = pblk[(int64_t)min(p + i, b - 1) * 81 + e];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v += p + i < b ? t[i] : 0.0;
+        }
+        sh[g][e] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 81) {
+        double v = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSumG; ++i) v += sh[i][e];
+        blk[(int64_t)lseg_blk[l] * 81 + e] = v;
+    }
+}
+
 // ---------------------------------------------------------------------------
-// diagonal stage: one wave per RCS row over the camera's observations
-// (four rows per workgroup); S_ii = sum J_c^T (I - K K^T) J_c +
+// diagonal stage: one workgroup per RCS row over the camera's observations;
+// S_ii = sum J_c^T (I - K K^T) J_c +
 // lambda diag(U), U = sum J_c^T J_c, b_i = -sum J_c^T (e + K lhat), then the
 // block-Jacobi inverse S_ii^-1 (Cholesky and triangular inverse).  A lane
 // holds 63 FP64 sums, which allows two waves per SIMD: with a wave per row a
 // CU works on eight rows at once, and while one lane of a wave factors its
 // row's block the other waves keep loading.
 // ---------------------------------------------------------------------------
-// one wave per workgroup, so that the three barriers hold a single wave
-// (on the 60,000-camera partition, FP64: 4.37 against 4.51 ms with four)
-constexpr int kDiagNW = 1;
+// NW waves (one workgroup) share a row's observations.  One where the rows
+// alone fill the chip, with barriers that hold a single wave (on the
+// 60,000-camera partition, FP64: 4.37 against 4.51 ms with four rows a
+// workgroup); four below kDiagRows rows, which leave most of the chip idle and
+// whose time is a row's serial chain of gathers (300 cameras of 840
+// observations: 24 against 31 us; 2,000 cameras: 96 against 90).
+constexpr int kDiagRows = 1024;
 
-template <typename T>
-__global__ __launch_bounds__(kDiagNW * kWave) void k_diag(int n_rows, const int32_t* __restrict__ rowobs_ptr,
+template <typename T, int NW>
+__global__ __launch_bounds__(NW * kWave) void k_diag(int n_rows, const int32_t* __restrict__ rowobs_ptr,
                                              const int32_t* __restrict__ rowobs, const int32_t* __restrict__ row_ptr,
                                              const T* __restrict__ R, const double* __restrict__ ebar, double lambda, double* __restrict__ blk, double* __restrict__ rhs,
                                              double* __restrict__ Minv, double* __restrict__ Linv,
                                              int* __restrict__ flags) {
-    __shared__ double sred[kDiagNW][64];
-    __shared__ double sS[kDiagNW][81];
-    __shared__ double sL[kDiagNW][81];
+    __shared__ double sred[NW][64];
+    __shared__ double S[81], sL[81], L[81];
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int row = blockIdx.x * kDiagNW + wv;
-    const bool live = row < n_rows;   // wave-uniform; every wave takes part in the barriers
-    double A[45], du[9], bb[9];
+    const int row = blockIdx.x;
+    double A[64];   // the 45 unique values of the block, diag(U) (9), the right-hand side (9)
 #pragma unroll
-    for (int m = 0; m < 45; ++m) A[m] = 0.0;
-#pragma unroll
-    for (int m = 0; m < 9; ++m) { du[m] = 0.0; bb[m] = 0.0; }
-    const int i0 = live ? rowobs_ptr[row] : 0, i1 = live ? rowobs_ptr[row + 1] : 0;
-    for (int idx = i0 + lane; idx < i1; idx += kWave) {
+    for (int m = 0; m < 64; ++m) A[m] = 0.0;
+    const int i0 = rowobs_ptr[row], i1 = rowobs_ptr[row + 1];
+    for (int idx = i0 + threadIdx.x; idx < i1; idx += NW * kWave) {
         const int k = rowobs[idx];
         double jc[18], K[6];
         const T* rk = R + (int64_t)k * kRec;
@@ -496,76 +529,40 @@ __global__ __launch_bounds__(kDiagNW * kWave) void k_diag(int n_rows, const int3
         int m = 0;
 #pragma unroll
         for (int r = 0; r < 9; ++r) {
-            du[r] += jc[r] * jc[r] + jc[9 + r] * jc[9 + r];
-            bb[r] -= jc[r] * v0 + jc[9 + r] * v1;
+            A[45 + r] += jc[r] * jc[r] + jc[9 + r] * jc[9 + r];
+            A[54 + r] -= jc[r] * v0 + jc[9 + r] * v1;
 #pragma unroll
             for (int c = r; c < 9; ++c, ++m) A[m] += jc[r] * q0[c] + jc[9 + r] * q1[c];
         }
     }
-    // the wave's 63 sums (fixed shuffle tree), each stored as soon as it is
-    // formed so that the totals do not occupy registers
+    sred[wv][lane] = wave_sums64(A);   // the wave's 63 sums
+    __syncthreads();
+    auto total = [&](int m) {   // value m over the waves, in order
+        double t = sred[0][m];
 #pragma unroll
-    for (int m = 0; m < 45; ++m) {
-        const double t = wave_sum(A[m]);
-        if (lane == 0) sred[wv][m] = t;
+        for (int w = 1; w < NW; ++w) t += sred[w][m];
+        return t;
+    };
+    for (int e = threadIdx.x; e < 81; e += NW * kWave) {
+        const int i = e / 9, j = e % 9;
+        const int a = i < j ? i : j, b = i < j ? j : i;
+        const int m = a * 9 - a * (a - 1) / 2 + (b - a);   // packed upper-triangle index
+        double v = total(m);
+        if (i == j) v += lambda * total(45 + i);
+        S[e] = v;
+        blk[(int64_t)row_ptr[row] * 81 + e] = v;
     }
-#pragma unroll
-    for (int m = 0; m < 9; ++m) {
-        const double t = wave_sum(du[m]), w = wave_sum(bb[m]);
-        if (lane == 0) { sred[wv][45 + m] = t; sred[wv][54 + m] = w; }
-    }
+    if (threadIdx.x < 9) rhs[(int64_t)row * 9 + threadIdx.x] = total(54 + threadIdx.x);
     __syncthreads();
-    double* S = sS[wv];
-    double* L = sL[wv];
-    if (live) {
-        for (int e = lane; e < 81; e += kWave) {
-            const int i = e / 9, j = e % 9;
-            const int a = i < j ? i : j, b = i < j ? j : i;
-            const int m = a * 9 - a * (a - 1) / 2 + (b - a);   // packed upper-triangle index
-            double v = sred[wv][m];
-            if (i == j) v += lambda * sred[wv][45 + i];
-            S[e] = v;
-            blk[(int64_t)row_ptr[row] * 81 + e] = v;
-        }
-        if (lane < 9) rhs[(int64_t)row * 9 + lane] = sred[wv][54 + lane];
-    }
+    if (wv == 0 && !wave_factor9(S, sL, L, lane) && lane == 0) flags[1] = 1;
     __syncthreads();
-    if (live && lane == 0) {
-        // Cholesky S = L L^T, then L^-1 in place (lower triangle)
-        bool ok = true;
-        for (int j = 0; j < 9; ++j) {
-            double sj = S[j * 9 + j];
-            for (int q = 0; q < j; ++q) sj -= L[j * 9 + q] * L[j * 9 + q];
-            if (!(sj > 0.0)) { ok = false; sj = 1.0; }
-            const double ljj = sqrt(sj);
-            L[j * 9 + j] = ljj;
-            for (int i = j + 1; i < 9; ++i) {
-                double t = S[i * 9 + j];
-                for (int q = 0; q < j; ++q) t -= L[i * 9 + q] * L[j * 9 + q];
-                L[i * 9 + j] = t / ljj;
-            }
-            for (int i = 0; i < j; ++i) L[i * 9 + j] = 0.0;
-        }
-        if (!ok) flags[1] = 1;
-        for (int j = 0; j < 9; ++j) {
-            L[j * 9 + j] = 1.0 / L[j * 9 + j];
-            for (int i = j + 1; i < 9; ++i) {
-                double t = 0.0;
-                for (int q = j; q < i; ++q) t -= L[i * 9 + q] * L[q * 9 + j];
-                L[i * 9 + j] = t / L[i * 9 + i];
-            }
-        }
-    }
-    __syncthreads();
-    if (live) {
-        // S^-1 = L^-T L^-1: entry (i, j) = sum_{q >= max(i,j)} Li[q][i] Li[q][j]
-        for (int e = lane; e < 81; e += kWave) {
-            const int i = e / 9, j = e % 9;
-            double t = 0.0;
-            for (int q = (i > j ? i : j); q < 9; ++q) t += L[q * 9 + i] * L[q * 9 + j];
-            Minv[(int64_t)row * 81 + e] = t;
-            Linv[(int64_t)row * 81 + e] = L[e];
-        }
+    // S^-1 = L^-T L^-1: entry (i, j) = sum_{q >= max(i,j)} Li[q][i] Li[q][j]
+    for (int e = threadIdx.x; e < 81; e += NW * kWave) {
+        const int i = e / 9, j = e % 9;
+        double t = 0.0;
+        for (int q = (i > j ? i : j); q < 9; ++q) t += L[q * 9 + i] * L[q * 9 + j];
+        Minv[(int64_t)row * 81 + e] = t;
+        Linv[(int64_t)row * 81 + e] = L[e];
     }
 }
 
@@ -1024,22 +1021,32 @@ void launch_offdiag(ba_ctx* c) {
         k_offdiag<double><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
                                                          (const double*)c->R, c->blk, c->pblk);
     if (c->n_lseg > 0) {
-        const int64_t n = (int64_t)c->n_lseg * 81;
-        k_pair_sum<<<(unsigned)((n + BS - 1) / BS), BS, 0, c->stream>>>(c->n_lseg, c->lseg_blk, c->lseg_ptr,
-                                                                        c->pblk, c->blk);
+        const int nl = c->n_lseg_long, ns = c->n_lseg - nl;
+        const int64_t n = (int64_t)ns * 81;
+        if (nl > 0) k_pair_sum_long<<<nl, 1024, 0, c->stream>>>(c->lseg_blk, c->lseg_ptr, c->pblk, c->blk);
+        if (ns > 0)
+            k_pair_sum<<<(unsigned)((n + BS - 1) / BS), BS, 0, c->stream>>>(ns, c->lseg_blk + nl, c->lseg_ptr + nl,
+                                                                            c->pblk, c->blk);
     }
+}
+
+template <typename T>
+void launch_diag_t(ba_ctx* c, double lambda) {
+    const T* R = (const T*)c->R;
+    if (c->n_rows < kDiagRows)
+        k_diag<T, 4><<<c->n_rows, 4 * kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr, R, c->ebar,
+                                                             lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags);
+    else
+        k_diag<T, 1><<<c->n_rows, kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr, R, c->ebar,
+                                                         lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags);
 }
 
 void launch_diag(ba_ctx* c, double lambda) {
     if (c->n_rows == 0) return;
     if (c->precision == BA_MIXED)
-        k_diag<float><<<(c->n_rows + kDiagNW - 1) / kDiagNW, kDiagNW * kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr,
-                                                       (const float*)c->R, c->ebar, lambda, c->blk, c->rhs,
-                                                       c->Minv, c->Linv, c->flags);
+        launch_diag_t<float>(c, lambda);
     else
-        k_diag<double><<<(c->n_rows + kDiagNW - 1) / kDiagNW, kDiagNW * kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr,
-                                                        (const double*)c->R, c->ebar, lambda, c->blk, c->rhs,
-                                                        c->Minv, c->Linv, c->flags);
+        launch_diag_t<double>(c, lambda);
 }
 
 // back-substitution; the model terms go to scal[2] (|J dx|^2) and scal[3]

@@ -254,96 +254,98 @@ __global__ __launch_bounds__(BS) void k_linpoint_s_long(int q0, const int32_t* _
     }
 }
 
-// Diagonal stage: one wave per RCS row over its records (the row's list):
-// diag(U) and b_u = -sum J^T (e + K lhat); then the diagonal block that the
-// pair stage formed gets lambda diag(U) and the identity on its padding,
-// and is factored (Cholesky, L^-1, block-Jacobi inverse).
-__global__ __launch_bounds__(BS) void k_node_diag(int n_rows, int n_free, const int32_t* __restrict__ rowobs_ptr,
+// diag(U) and -J^T (e + K lhat) of record a, added to v[0..8] and v[9..17]
+__device__ __forceinline__ void add_node_terms(const double* __restrict__ R, const double* __restrict__ ebar, int a,
+                                               double* v) {
+    double jc[18];
+    load_jc(R + (int64_t)a * kRec, jc);
+    const double2 e = reinterpret_cast<const double2*>(ebar)[a >> 1];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) {
+        v[c] += jc[c] * jc[c] + jc[9 + c] * jc[9 + c];
+        v[9 + c] -= jc[c] * e.x + jc[9 + c] * e.y;
+    }
+}
+
+// The physical cameras' sums by slices of their record lists (a camera takes
+// every observation of its images: with one wave per row the 4 cameras of an
+// 80-image block took 417 us, both kernels 31 now): one workgroup per slice of up to `len` records, part[slice][18].
+__global__ __launch_bounds__(BS) void k_node_part(int n_free, int len, const int32_t* __restrict__ slice_cam,
+                                                  const int32_t* __restrict__ slice_beg,
+                                                  const int32_t* __restrict__ rowobs_ptr,
+                                                  const int32_t* __restrict__ rowobs, const double* __restrict__ R,
+                                                  const double* __restrict__ ebar, double* __restrict__ part) {
+    __shared__ double sh[18][WPB];
+    const int i0 = slice_beg[blockIdx.x];
+    const int i1 = min(i0 + len, rowobs_ptr[n_free + slice_cam[blockIdx.x] + 1]);
+    double v[18];
+#pragma unroll
+    for (int m = 0; m < 18; ++m) v[m] = 0.0;
+    for (int idx = i0 + threadIdx.x; idx < i1; idx += BS) add_node_terms(R, ebar, rowobs[idx], v);
+    block_reduce<18>(v, sh);
+    if (threadIdx.x == 0)
+#pragma unroll
+        for (int m = 0; m < 18; ++m) part[(int64_t)blockIdx.x * 18 + m] = v[m];
+}
+
+// Diagonal stage: one workgroup per RCS row.  An image's row sums diag(U) and
+// b_u = -sum J^T (e + K lhat) over its records, a camera's over its slices'
+// sums; then the diagonal block that the pair stage formed gets
+// lambda diag(U) and the identity on its padding, and is factored
+// (Cholesky, L^-1, block-Jacobi inverse).
+__global__ __launch_bounds__(BS) void k_node_diag(int n_free, const int32_t* __restrict__ rowobs_ptr,
                                                   const int32_t* __restrict__ rowobs,
                                                   const int32_t* __restrict__ row_ptr, const double* __restrict__ R,
-                                                  const double* __restrict__ ebar, double lambda,
+                                                  const double* __restrict__ ebar,
+                                                  const int32_t* __restrict__ slice_ptr,
+                                                  const double* __restrict__ part, double lambda,
                                                   double* __restrict__ blk, double* __restrict__ rhs,
                                                   double* __restrict__ Minv, double* __restrict__ Linv,
                                                   int* __restrict__ flags) {
-    __shared__ double sred[WPB][18];
-    __shared__ double sS[WPB][81];
-    __shared__ double sL[WPB][81];
-    const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int row = blockIdx.x * WPB + wv;
-    const bool live = row < n_rows;
-    double du[9], bb[9];
+    __shared__ double sh[18][WPB];
+    __shared__ double S[81], sL[81], L[81];
+    const int lane = threadIdx.x % kWave;
+    const int row = blockIdx.x;
+    double v[18];
 #pragma unroll
-    for (int m = 0; m < 9; ++m) { du[m] = 0.0; bb[m] = 0.0; }
-    const int i0 = live ? rowobs_ptr[row] : 0, i1 = live ? rowobs_ptr[row + 1] : 0;
-    for (int idx = i0 + lane; idx < i1; idx += kWave) {
-        const int a = rowobs[idx];
-        double jc[18];
-        load_jc(R + (int64_t)a * kRec, jc);
-        const double2 v = reinterpret_cast<const double2*>(ebar)[a >> 1];
+    for (int m = 0; m < 18; ++m) v[m] = 0.0;
+    if (row < n_free) {
+        const int i0 = rowobs_ptr[row], i1 = rowobs_ptr[row + 1];
+        for (int idx = i0 + threadIdx.x; idx < i1; idx += BS) add_node_terms(R, ebar, rowobs[idx], v);
+    } else {
+        const int s0 = slice_ptr[row - n_free], s1 = slice_ptr[row - n_free + 1];
+        for (int s = s0 + threadIdx.x; s < s1; s += BS)
 #pragma unroll
-        for (int c = 0; c < 9; ++c) {
-            du[c] += jc[c] * jc[c] + jc[9 + c] * jc[9 + c];
-            bb[c] -= jc[c] * v.x + jc[9 + c] * v.y;
-        }
+            for (int m = 0; m < 18; ++m) v[m] += part[(int64_t)s * 18 + m];
     }
-#pragma unroll
-    for (int m = 0; m < 9; ++m) {
-        const double t = wave_sum(du[m]), w = wave_sum(bb[m]);
-        if (lane == 0) { sred[wv][m] = t; sred[wv][9 + m] = w; }
-    }
-    __syncthreads();
-    double* S = sS[wv];
-    double* L = sL[wv];
+    block_reduce<18>(v, sh);
     const int nreal = row < n_free ? 6 : 5;
-    if (live) {
-        // the pair stage summed the (a, b) and (b, a) terms of this block in
-        // separate lanes: the mean with the transpose makes it exactly symmetric
-        const double* B = blk + (int64_t)row_ptr[row] * 81;
-        for (int e = lane; e < 81; e += kWave) {
-            const int i = e / 9, j = e % 9;
-            double v = 0.5 * (B[e] + B[j * 9 + i]);
-            if (i == j) v = i < nreal ? B[e] + lambda * sred[wv][i] : 1.0;
-            S[e] = v;
-        }
-        if (lane < 9) rhs[(int64_t)row * 9 + lane] = sred[wv][9 + lane];
+    // the pair stage summed the (a, b) and (b, a) terms of this block in
+    // separate lanes: the mean with the transpose makes it exactly symmetric
+    double* B = blk + (int64_t)row_ptr[row] * 81;
+    for (int e = threadIdx.x; e < 81; e += BS) {
+        const int i = e / 9, j = e % 9;
+        double w = 0.5 * (B[e] + B[j * 9 + i]);
+        if (i == j) w = i < nreal ? B[e] : 1.0;
+        S[e] = w;
     }
     __syncthreads();
-    if (live)
-        for (int e = lane; e < 81; e += kWave) blk[(int64_t)row_ptr[row] * 81 + e] = S[e];
-    if (live && lane == 0) {
-        bool ok = true;
-        for (int j = 0; j < 9; ++j) {
-            double sj = S[j * 9 + j];
-            for (int q = 0; q < j; ++q) sj -= L[j * 9 + q] * L[j * 9 + q];
-            if (!(sj > 0.0)) { ok = false; sj = 1.0; }
-            const double ljj = sqrt(sj);
-            L[j * 9 + j] = ljj;
-            for (int i = j + 1; i < 9; ++i) {
-                double t = S[i * 9 + j];
-                for (int q = 0; q < j; ++q) t -= L[i * 9 + q] * L[j * 9 + q];
-                L[i * 9 + j] = t / ljj;
-            }
-            for (int i = 0; i < j; ++i) L[i * 9 + j] = 0.0;
+#pragma unroll
+    for (int m = 0; m < 9; ++m)
+        if (threadIdx.x == m) {
+            if (m < nreal) S[m * 10] += lambda * v[m];
+            rhs[(int64_t)row * 9 + m] = v[9 + m];
         }
-        if (!ok) flags[1] = 1;
-        for (int j = 0; j < 9; ++j) {
-            L[j * 9 + j] = 1.0 / L[j * 9 + j];
-            for (int i = j + 1; i < 9; ++i) {
-                double t = 0.0;
-                for (int q = j; q < i; ++q) t -= L[i * 9 + q] * L[q * 9 + j];
-                L[i * 9 + j] = t / L[i * 9 + i];
-            }
-        }
-    }
     __syncthreads();
-    if (live) {
-        for (int e = lane; e < 81; e += kWave) {
-            const int i = e / 9, j = e % 9;
-            double t = 0.0;
-            for (int q = (i > j ? i : j); q < 9; ++q) t += L[q * 9 + i] * L[q * 9 + j];
-            Minv[(int64_t)row * 81 + e] = t;
-            Linv[(int64_t)row * 81 + e] = L[e];
-        }
+    for (int e = threadIdx.x; e < 81; e += BS) B[e] = S[e];
+    if (threadIdx.x < kWave && !wave_factor9(S, sL, L, lane) && lane == 0) flags[1] = 1;
+    __syncthreads();
+    for (int e = threadIdx.x; e < 81; e += BS) {
+        const int i = e / 9, j = e % 9;
+        double t = 0.0;
+        for (int q = (i > j ? i : j); q < 9; ++q) t += L[q * 9 + i] * L[q * 9 + j];
+        Minv[(int64_t)row * 81 + e] = t;
+        Linv[(int64_t)row * 81 + e] = L[e];
     }
 }
 
@@ -535,9 +537,15 @@ void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, 
 
 void launch_node_diag(ba_ctx* c, double lambda) {
     if (c->n_rows == 0) return;
-    k_node_diag<<<(c->n_rows + WPB - 1) / WPB, BS, 0, c->stream>>>(c->n_rows, c->n_free, c->rowobs_ptr, c->rowobs,
-                                                                   c->row_ptr, (const double*)c->R, c->ebar, lambda,
-                                                                   c->blk, c->rhs, c->Minv, c->Linv, c->flags);
+    double* part = c->pcg.W;
+    if (18 * (int64_t)c->n_slice > 63 * (int64_t)c->n_rows)
+        throw ba_hip_error(hipErrorInvalidValue, "slice sums exceed their buffer", __FILE__, __LINE__);
+    if (c->n_slice > 0)
+        k_node_part<<<c->n_slice, BS, 0, c->stream>>>(c->n_free, c->node_len, c->slice_cam, c->slice_beg,
+                                                      c->rowobs_ptr, c->rowobs, (const double*)c->R, c->ebar, part);
+    k_node_diag<<<c->n_rows, BS, 0, c->stream>>>(
+        c->n_free, c->rowobs_ptr, c->rowobs, c->row_ptr, (const double*)c->R, c->ebar, c->slice_ptr, part,
+        lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags);
 }
 
 void launch_back_substitute_shared(ba_ctx* c, const double* dxc, double* dxp) {
