@@ -173,9 +173,10 @@ typedef struct ba_pcg_opts {
  * sums them per row in a fixed order (72 extra bytes written and read per
  * block, against 648 (FP64) or 324 (FP32) bytes of a second block read).
  * Both are deterministic; they differ only in the summation order.  AUTO
- * takes UPPER when the copy of both triangles would exceed 256 MiB (about
- * the GPU's last-level cache), FULL otherwise (one kernel less per
- * iteration on small systems).  A factorised preconditioner (FSAI or the
+ * takes UPPER when the copy of both triangles would exceed 128 MiB (256 MiB,
+ * about the GPU's last-level cache, with a factorised preconditioner), FULL
+ * otherwise (one kernel less per iteration; the smallest systems are solved
+ * by one kernel that holds S in registers).  A factorised preconditioner (FSAI or the
  * learned factor, M^-1 = G^T G) is applied with the same layout: FULL reads
  * G (FP32) by rows and a transposed copy; UPPER reads each block of G once
  * from an FP16 copy (G D^-1 with D = diag(S)^-1/2, one FP32 scale per

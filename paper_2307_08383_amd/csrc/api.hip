@@ -759,11 +759,16 @@ ba_status form_rcs_async(ba_ctx* c, double lambda, bool point_done = false) {
 size_t n_params(const ba_ctx* c) { return 6 * (size_t)c->n_cams + 5 * (size_t)c->n_phys; }
 
 // selects the S copy and the product layout of the next solve (allocating
-// the FP32 copies on first use)
-void select_solver_matrix(ba_ctx* c, int fp32, int product) {
+// the FP32 copies on first use).  AUTO: FULL needs one kernel less an
+// iteration, UPPER reads each block once; with a block-diagonal M they break
+// even near 128 MiB of FULL copy (FP64, us an iteration FULL / UPPER: 92 MiB
+// 29.7 / 29.5, 136 MiB 36.4 / 34.0, 242 MiB 54.6 / 44.4; FP32: 121 MiB 37.0 /
+// 36.0, 138 MiB 39.2 / 39.3, 182 MiB 48.9 / 46.8).  A factorised M is stored
+// by the layout too (UPPER in FP16) and keeps the limit of 256 MiB.
+void select_solver_matrix(ba_ctx* c, int fp32, int product, bool factorised) {
     c->s32 = fp32 ? 1 : 0;
     const double full_bytes = (double)c->n_sf * 81 * (c->s32 ? sizeof(float) : sizeof(double));
-    c->upper = (product == BA_PRODUCT_UPPER || (product == BA_PRODUCT_AUTO && full_bytes > 256.0 * (1 << 20))) ? 1 : 0;
+    c->upper = (product == BA_PRODUCT_UPPER || (product == BA_PRODUCT_AUTO && full_bytes > (factorised ? 256.0 : 128.0) * (1 << 20))) ? 1 : 0;
     if (c->s32 && !c->Sf32) dalloc(c, &c->Sf32, (size_t)std::max<int64_t>(c->n_sf, 1) * 81);
     if (c->upper && c->s32 && !c->Su32) dalloc(c, &c->Su32, (size_t)c->n_blk * 81);
 }
@@ -1263,7 +1268,8 @@ ba_status ba_pcg_solve(ba_ctx* c, const ba_pcg_opts* o, double* dxc, ba_pcg_info
     return guarded(c, [&]() {
         int it = 0;
         double rr = 0.0;
-        select_solver_matrix(c, o ? o->solver_fp32 : 0, o ? o->product : BA_PRODUCT_AUTO);
+        select_solver_matrix(c, o ? o->solver_fp32 : 0, o ? o->product : BA_PRODUCT_AUTO,
+                             pre == BA_PRECOND_FSAI || pre == BA_PRECOND_LEARNED_FSAI);
         if (pre == BA_PRECOND_LEARNED && c->n_rows > 0) prepare_learned(c);
         if (pre == BA_PRECOND_FSAI && c->n_rows > 0) prepare_fsai(c);
         if (pre == BA_PRECOND_LEARNED_FSAI && c->n_rows > 0) prepare_learned_fsai(c);
@@ -1310,7 +1316,7 @@ ba_status ba_rcs_product(ba_ctx* c, const double* x, double* y, int32_t product,
             BA_HIP_CHECK(hipStreamSynchronize(c->stream));
             return BA_OK;
         }
-        select_solver_matrix(c, solver_fp32, product);
+        select_solver_matrix(c, solver_fp32, product, false);
         ba::launch_product(c, x, y);
         BA_HIP_CHECK(hipGetLastError());
         BA_HIP_CHECK(hipStreamSynchronize(c->stream));
@@ -1394,7 +1400,8 @@ ba_status ba_lm_step(ba_ctx* c, double* cams, double* pts, ba_lm_state* st, cons
         double rr = 0.0;
         ba_status ps = BA_OK;
         BA_HIP_CHECK(hipEventRecord(ev[14], c->stream));
-        select_solver_matrix(c, o ? o->solver_fp32 : 0, o ? o->product : BA_PRODUCT_AUTO);
+        select_solver_matrix(c, o ? o->solver_fp32 : 0, o ? o->product : BA_PRODUCT_AUTO,
+                             pre == BA_PRECOND_FSAI || pre == BA_PRECOND_LEARNED_FSAI);
         if (pre == BA_PRECOND_LEARNED && c->n_rows > 0) prepare_learned(c);
         if (pre == BA_PRECOND_FSAI && c->n_rows > 0) prepare_fsai(c);
         if (pre == BA_PRECOND_LEARNED_FSAI && c->n_rows > 0) prepare_learned_fsai(c);
