@@ -293,16 +293,17 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // r, in record order of a, then b; grouped by the row s of b into
     // segments, one per block (r, s) (s = r: the diagonal block); inside the
     // row the segments are ordered longest first (ties by column), so that
-    // lanes sharing a wavefront get similar amounts of work.  Blocks of a
+    // lanes sharing a wavefront get similar amounts of work, and with tiles
+    // (below) a segment's couples by tile, then record order.  Blocks of a
     // row: the diagonal, then the columns s > r in ascending order.
     std::vector<int32_t> rq(n_rec);   // internal point of each record
     parallel_for(np, 1 << 14, [&](int64_t q0, int64_t q1, int) {
         for (int64_t q = q0; q < q1; ++q)
             for (int32_t a = rptr[q]; a < rptr[q + 1]; ++a) rq[a] = (int32_t)q;
     });
-    auto scan_row = [&](int32_t r, auto&& visit) {
-        for (int32_t i = rowobs_ptr[r]; i < rowobs_ptr[r + 1]; ++i) {
-            const int32_t a = rowobs[i], q = rq[a];
+    auto scan_row = [&](int32_t r, const int32_t* recs, auto&& visit) {
+        for (int32_t i = 0; i < rowobs_ptr[r + 1] - rowobs_ptr[r]; ++i) {
+            const int32_t a = recs[i], q = rq[a];
             for (int32_t b = shared ? rptr[q] : a + 1; b < rptr[q + 1]; ++b) {
                 const int32_t rb = rrow[b];
                 if (rb < 0 || (shared && rb < r)) continue;
@@ -319,7 +320,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         std::vector<int32_t>& cnt_s = t_cnt[t];
         std::vector<int32_t>& touch = t_touch[t];
         int64_t m = 0;
-        scan_row(r, [&](int32_t, int32_t, int32_t s) {
+        scan_row(r, rowobs.data() + rowobs_ptr[r], [&](int32_t, int32_t, int32_t s) {
             if (cnt_s[s]++ == 0) touch.push_back(s);
             ++m;
         });
@@ -327,14 +328,16 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     };
     std::vector<int64_t> ctr(nr + 1, 0), row_ptr(nr + 1, 0);
     std::vector<int32_t> sptr(nr + 1, 0);
+    std::vector<std::vector<int32_t>> cols(nr);   // each row's columns s > r, ascending
     parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
         for (int64_t r = r0; r < r1; ++r) {
             ctr[r + 1] = count_row((int32_t)r, t);
             int32_t nb = 1;
             for (int32_t s2 : t_touch[t]) {
-                if (s2 != r) ++nb;
+                if (s2 != r) { ++nb; cols[r].push_back(s2); }
                 t_cnt[t][s2] = 0;
             }
+            std::sort(cols[r].begin(), cols[r].end());
             sptr[r + 1] = (int32_t)t_touch[t].size();
             row_ptr[r + 1] = nb;
             t_touch[t].clear();
@@ -349,9 +352,82 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     if (ntr > INT32_MAX) throw ba_invalid{"too many camera-pair couples for 32-bit indices"};
     if (row_ptr[nr] > INT32_MAX) throw ba_invalid{"too many RCS blocks for 32-bit indices"};
     const int32_t nseg = sptr[nr];
+    // Camera clusters, which the order of the pair stage's work follows:
+    // breadth-first growth over the co-visibility graph from the lowest
+    // unassigned row, up to a budget of record bytes.  A point's track is read
+    // by the rows of each of its cameras; inside a compact cluster those rows
+    // run close together on one XCD, so the track's records come from L2 / MALL
+    // instead of HBM after the first of them.
+    //   Up to kTileMin of records, twice what the MALL holds, a camera
+    // pair's couples stay together and clusters of about 4 MB, an XCD's L2,
+    // order the pairs.  Beyond it the couples are worked through by tiles, the
+    // points whose first free row lies in one cluster, of about 1 MB: a pair's
+    // couples are ordered by tile and cut between tiles into units, and an XCD
+    // works on one tile's units at a time, whose records it then reads from HBM
+    // once.  The pair stage and the sums of the cut pairs, start's order against
+    // tiles of 4, 2, 1 and 0.5 MB: 15,000 cameras, FP64, 4.8 GB of records: 3,108
+    // against 2,835, 2,738, 2,720 and 2,720 us; 18,000 cameras, FP32, 1.7 GB:
+    // 1,467 against 1,435, 1,407, 1,404 and 1,407; 2,000 cameras, FP64, 460 MB:
+    // 228 against 228 and (2 MB) 230.
+    const double rec_bytes = (double)kRec * (c->precision == BA_MIXED ? sizeof(float) : sizeof(double));
+    constexpr double kTileMin = 512.0 * (1 << 20);
+    const bool tiled = rec_bytes * (double)n_rec > kTileMin;
+    std::vector<int32_t> clus(nr, -1);
+    {
+        std::vector<int32_t> adj_ptr(nr + 1, 0), adj;
+        for (int32_t r = 0; r < nr; ++r)
+            for (int32_t s2 : cols[r]) {
+                adj_ptr[r + 1]++;
+                adj_ptr[s2 + 1]++;
+            }
+        for (int32_t r = 0; r < nr; ++r) adj_ptr[r + 1] += adj_ptr[r];
+        adj.resize(adj_ptr[nr]);
+        {
+            std::vector<int32_t> fill(adj_ptr.begin(), adj_ptr.end() - 1);
+            for (int32_t r = 0; r < nr; ++r)
+                for (int32_t s2 : cols[r]) {
+                    adj[fill[r]++] = s2;
+                    adj[fill[s2]++] = r;
+                }
+        }
+        std::vector<int64_t> row_obs(nr, 0);
+        for (int64_t k = 0; k < n_rec; ++k)
+            if (rrow[k] >= 0) row_obs[rrow[k]]++;
+        const double budget = (tiled ? 1.0 : 4.0) * (1 << 20);
+        std::vector<int32_t> queue;
+        int32_t n_cl = 0;
+        for (int32_t s0 = 0; s0 < nr; ++s0) {
+            if (clus[s0] >= 0) continue;
+            queue.assign(1, s0);
+            clus[s0] = n_cl;
+            double bytes = 0.0;
+            for (size_t h = 0; h < queue.size() && bytes < budget; ++h) {
+                const int32_t r = queue[h];
+                bytes += (double)row_obs[r] * rec_bytes;
+                for (int32_t e = adj_ptr[r]; e < adj_ptr[r + 1] && bytes < budget; ++e)
+                    if (clus[adj[e]] < 0) {
+                        clus[adj[e]] = n_cl;
+                        queue.push_back(adj[e]);
+                    }
+            }
+            ++n_cl;
+        }
+    }
+    // tile of each point: the cluster of the first free row that sees it
+    std::vector<int32_t> tile;
+    if (tiled) {
+        tile.assign(np, 0);
+        parallel_for(np, 1 << 14, [&](int64_t q0, int64_t q1, int) {
+            for (int64_t q = q0; q < q1; ++q)
+                for (int32_t a = rptr[q]; a < rptr[q + 1]; ++a)
+                    if (rrow[a] >= 0) { tile[q] = clus[rrow[a]]; break; }
+        });
+    }
+    ph.mark("clusters");
     std::vector<int32_t> trip(2 * (size_t)ntr), col_idx(row_ptr[nr]);
     std::vector<int32_t> off_blk(nseg), pair_ptr(nseg + 1), seg_row(nseg);
     parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
+        std::vector<int32_t> recs;   // the row's records by tile, in record order inside a tile
         std::vector<int32_t>& cnt_s = t_cnt[t];
         std::vector<int32_t>& blk_s = t_blk[t];
         std::vector<int64_t>& pos_s = t_pos[t];
@@ -380,7 +456,10 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
                 m += cnt_s[s2];
                 ++sg;
             }
-            scan_row((int32_t)r, [&](int32_t a, int32_t b, int32_t s2) {
+            recs.assign(rowobs.begin() + rowobs_ptr[r], rowobs.begin() + rowobs_ptr[r + 1]);
+            if (tiled)
+                std::stable_sort(recs.begin(), recs.end(), [&](int32_t x, int32_t y) { return tile[rq[x]] < tile[rq[y]]; });
+            scan_row((int32_t)r, recs.data(), [&](int32_t a, int32_t b, int32_t s2) {
                 const int64_t d = pos_s[s2]++;
                 trip[2 * d] = a;
                 trip[2 * d + 1] = b;
@@ -390,7 +469,6 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         }
     });
     pair_ptr[nseg] = (int32_t)ntr;
-    std::vector<int32_t>().swap(rq);
     c->n_blk = row_ptr[nr];
     c->n_offseg = nseg;
     c->n_pairs = ntr;
@@ -402,88 +480,64 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // quarter of the average work of one of the lane groups the chip holds at
     // once (256 CUs x 16 waves x 4 groups), at least 8 steps of 4 couples.
     // A wave runs until the longest of its four units ends, so inside each
-    // camera cluster (below) the units are ordered longest first (neighbouring
+    // cluster or tile the units are ordered longest first (neighbouring
     // units have similar lengths); the waves are then cut into 8 contiguous
     // ranges of equal work, one per XCD.
-    // The order of the units follows camera clusters: breadth-first growth
-    // over the co-visibility graph from the lowest unassigned row, up to
-    // about 4 MB of records per cluster (an XCD's L2; 1, 2, 16 and 64 MB
-    // measured slower).  A point's track is read by the rows
-    // of each of its cameras; inside a compact cluster those rows run close
-    // together on one XCD, so the track's records come from L2 / MALL instead
-    // of HBM after the first of them.
-    std::vector<int32_t> clus(nr, -1);
-    {
-        std::vector<int32_t> adj_ptr(nr + 1, 0), adj;
-        for (int32_t r = 0; r < nr; ++r)
-            for (int64_t kb = row_ptr[r] + 1; kb < row_ptr[r + 1]; ++kb) {
-                adj_ptr[r + 1]++;
-                adj_ptr[col_idx[kb] + 1]++;
-            }
-        for (int32_t r = 0; r < nr; ++r) adj_ptr[r + 1] += adj_ptr[r];
-        adj.resize(adj_ptr[nr]);
-        {
-            std::vector<int32_t> fill(adj_ptr.begin(), adj_ptr.end() - 1);
-            for (int32_t r = 0; r < nr; ++r)
-                for (int64_t kb = row_ptr[r] + 1; kb < row_ptr[r + 1]; ++kb) {
-                    adj[fill[r]++] = col_idx[kb];
-                    adj[fill[col_idx[kb]]++] = r;
-                }
-        }
-        std::vector<int64_t> row_obs(nr, 0);
-        for (int64_t k = 0; k < n_rec; ++k)
-            if (rrow[k] >= 0) row_obs[rrow[k]]++;
-        const double rec = (double)kRec * (c->precision == BA_MIXED ? sizeof(float) : sizeof(double));
-        // one XCD's L2 (budgets of 1 to 16 MiB time alike on the 60,000-image
-        // partition workload)
-        const double budget = 4.0 * (1 << 20);
-        std::vector<int32_t> queue;
-        int32_t n_cl = 0;
-        for (int32_t s0 = 0; s0 < nr; ++s0) {
-            if (clus[s0] >= 0) continue;
-            queue.assign(1, s0);
-            clus[s0] = n_cl;
-            double bytes = 0.0;
-            for (size_t h = 0; h < queue.size() && bytes < budget; ++h) {
-                const int32_t r = queue[h];
-                bytes += (double)row_obs[r] * rec;
-                for (int32_t e = adj_ptr[r]; e < adj_ptr[r + 1] && bytes < budget; ++e)
-                    if (clus[adj[e]] < 0) {
-                        clus[adj[e]] = n_cl;
-                        queue.push_back(adj[e]);
-                    }
-            }
-            ++n_cl;
-        }
-    }
-    ph.mark("clusters");
     std::vector<int32_t> unit_rng, unit_dst, lseg_blk, lseg_ptr{0};
     {
         struct Unit { int32_t win, t0, t1, dst; };
-        std::vector<Unit> units;
         int64_t steps = 0;
         for (int32_t sg = 0; sg < c->n_offseg; ++sg) steps += (pair_ptr[sg + 1] - pair_ptr[sg] + 3) / 4;
         const int64_t groups = 256 * 16 * 4;
         const int64_t cap = 4 * std::max<int64_t>(8, steps / (4 * groups));
-        int32_t n_p = 0;
-        // segments of more than kLongSeg chunks first
+        c->unit_steps = steps;
+        // The pieces of segment sg, emit(t0, t1, window): cut where the tile
+        // changes, but not into pieces of fewer than kMinRun couples (four
+        // steps; a piece costs a start, a reduction and 1,300 bytes of partial
+        // block; 8 and 32 time alike), then by the cap.
+        constexpr int32_t kMinRun = 16;
+        auto pieces = [&](int32_t sg, auto&& emit) {
+            const int32_t a = pair_ptr[sg], b = pair_ptr[sg + 1];
+            int32_t lo = a;
+            while (lo < b) {
+                int32_t hi = b;
+                if (tiled && b - lo >= 2 * kMinRun)
+                    for (int32_t t = lo + kMinRun; t <= b - kMinRun; ++t)
+                        if (tile[rq[trip[2 * (size_t)t]]] != tile[rq[trip[2 * (size_t)t - 2]]]) { hi = t; break; }
+                const int32_t w = tiled ? tile[rq[trip[2 * (size_t)((lo + hi) / 2)]]] : clus[seg_row[sg]];
+                for (int64_t t = lo; t < hi; t += cap) emit((int32_t)t, (int32_t)std::min<int64_t>(t + cap, hi), w);
+                lo = hi;
+            }
+        };
+        std::vector<int32_t> n_piece(nseg);
+        parallel_for(nseg, 256, [&](int64_t s0, int64_t s1, int) {
+            for (int64_t sg = s0; sg < s1; ++sg) pieces((int32_t)sg, [&](int32_t, int32_t, int32_t) { ++n_piece[sg]; });
+        });
+        // first unit and first partial block of each segment; split segments
+        // of more than kLongSeg pieces come first in the list
+        std::vector<int32_t> u0(nseg), p0(nseg, -1);
+        int32_t n_p = 0, n_u = 0;
+        for (int32_t sg = 0; sg < nseg; ++sg) { u0[sg] = n_u; n_u += n_piece[sg]; }
         for (int pass = 0; pass < 2; ++pass) {
-          for (int32_t sg = 0; sg < c->n_offseg; ++sg) {
-            const int32_t a = pair_ptr[sg], b = pair_ptr[sg + 1], w = clus[seg_row[sg]];
-            if ((b - a > ba::kLongSeg * cap) != (pass == 0)) continue;
-            if (b - a <= cap) {
-                units.push_back({w, a, b, off_blk[sg]});
-                continue;
+            for (int32_t sg = 0; sg < nseg; ++sg) {
+                if (n_piece[sg] < 2 || (n_piece[sg] > ba::kLongSeg) != (pass == 0)) continue;
+                p0[sg] = n_p;
+                n_p += n_piece[sg];
+                lseg_blk.push_back(off_blk[sg]);
+                lseg_ptr.push_back(n_p);
             }
-            for (int64_t t = a; t < b; t += cap) {
-                units.push_back({w, (int32_t)t, (int32_t)std::min<int64_t>(t + cap, b), -(n_p + 1)});
-                ++n_p;
-            }
-            lseg_blk.push_back(off_blk[sg]);
-            lseg_ptr.push_back(n_p);
-          }
-          if (pass == 0) c->n_lseg_long = (int32_t)lseg_blk.size();
+            if (pass == 0) c->n_lseg_long = (int32_t)lseg_blk.size();
         }
+        std::vector<Unit> units(n_u);
+        parallel_for(nseg, 256, [&](int64_t s0, int64_t s1, int) {
+            for (int64_t sg = s0; sg < s1; ++sg) {
+                int32_t i = 0;
+                pieces((int32_t)sg, [&](int32_t t0, int32_t t1, int32_t w) {
+                    units[u0[sg] + i] = {w, t0, t1, p0[sg] < 0 ? off_blk[sg] : -(p0[sg] + i + 1)};
+                    ++i;
+                });
+            }
+        });
         std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) {
             return x.win != y.win ? x.win < y.win : x.t1 - x.t0 > y.t1 - y.t0;
         });
@@ -512,6 +566,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         c->n_lseg = (int32_t)lseg_blk.size();
         c->n_pblk = n_p;
     }
+    std::vector<int32_t>().swap(rq);
     ph.mark("units");
     c->h_blk_pairs.assign(c->n_blk, 0);
     for (int32_t sg = 0; sg < c->n_offseg; ++sg)

@@ -517,6 +517,7 @@ struct ba_ctx {
     // each) [xcd_wv[x], xcd_wv[x+1]) run on XCD x.
     // the first n_lseg_long split segments have more than kLongSeg chunks
     int32_t n_unit = 0, n_lseg = 0, n_lseg_long = 0, n_pblk = 0;
+    int64_t unit_steps = 0;        // their steps of four couples in all
     int32_t xcd_wv[9] = {0};
     int32_t *unit_rng = nullptr, *unit_dst = nullptr, *lseg_blk = nullptr, *lseg_ptr = nullptr;
     double* pblk = nullptr;            // [n_pblk][81]

@@ -299,38 +299,59 @@ __global__ __launch_bounds__(kLinNW * kWave) void k_linpoint_d(int n_chunk, cons
 // lane accumulates the 9 rows of its columns of
 //   S_ij -= J_ca^T (K_a K_b^T) J_cb
 // over the couples of its slot, then the 4 slots are reduced by shuffles.
-// A lane group works on one unit: a whole segment, or a chunk of a long one
-// whose partial block is summed by k_pair_sum.  A step covers the wave's 16
+// A lane group works on one unit: a whole segment, or a piece of one whose
+// partial block is summed by k_pair_sum.  A step covers the wave's 16
 // couples; their two records are copied from global memory straight into LDS
 // (16-byte lane copies that bypass the registers, spread over the whole wave,
 // so every record is fetched once per step instead of once per lane of its
-// couple).  The copies of step s + 1 are issued before step s is computed
-// from the other of two LDS buffers.  A buffer is chunk-major: 16-byte chunk
-// h of couple i sits at slot h * 16 + i, so the 16 couples' copies of one
-// value lie in consecutive banks.  Units are stored in windows of rows
-// (longest first inside a window); workgroup b runs on XCD b mod 8, which
-// takes the waves of its own contiguous range of rows (ranges of equal work),
-// keeping the records of neighbouring cameras in its L2.
+// couple).
+//   What bounds it: the records' way from L2 and HBM, 384 (FP32: 192) bytes a
+// couple, behind a latency of two microseconds under load.  So the copies of
+// the next kBuf - 1 steps are in flight while a step is computed, from kBuf
+// LDS buffers.  The buffers are separate arrays and the loop is unrolled by
+// them: reads of one array of buffers made the compiler wait for every copy
+// in flight before each step.  The couples' indices are read kBuf steps
+// before their copies are issued, so that waiting for an index never waits
+// for a younger copy, and the single wave needs no barrier.
+//   Four neighbouring lanes copy the four 16-byte chunks of one 64-byte piece
+// of a record (one address a cycle otherwise: 2,982 against 3,044 us, 207
+// against 221 us below), and a couple's piece lies rotated by its lane group
+// (chunk h at slot h ^ group), so that the wave's 16 couples read one value
+// from 16 different bank quads.
+//   Measured: 15,000 cameras, 57.6 M couples, FP64 3,500 -> 2,660 us with the
+// tiles described where the units are built; 18,000 cameras, 42.4 M couples,
+// FP32 records 1,707 -> 1,371 us; 2,000 cameras, 3.8 M couples, FP64 229 -> 207.
+//   Units are stored by tiles or clusters of cameras (longest first inside
+// each); workgroup b runs on XCD b mod 8, which takes the waves of its own
+// contiguous range of units (ranges of equal work), keeping the records of
+// neighbouring cameras in its L2.
 // ---------------------------------------------------------------------------
-constexpr int kPairWave = 4;   // units (camera pairs or chunks) per wave
+constexpr int kPairWave = 4;   // units (camera pairs or pieces) per wave
 
 struct XcdRanges { int wv[9]; };
 
-// Three waves per SIMD: the FP64 instance's two 6 KB LDS buffers allow no
-// more (12 per CU), and asking for four made the compiler spill to fit 128
-// registers (12.26 against 12.14 ms on the 60,000-camera partition).
-template <typename T, bool SUB = false>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3))) void k_offdiag(
+// Buffers: two, which the FP64 instance's 6 KB each allow to 12 waves a CU
+// (three a SIMD; asking for four makes the compiler spill).  FP64 with three
+// buffers and 8 waves where units are long (kDeepSteps steps on average): 2,644
+// against 2,815 us at 25 steps a unit, 218 against 207 at 10, where starting
+// and reducing a unit weighs more than the copies' latency.  FP32: two and
+// 12 waves (1,420 us) against three (1,454) and four (1,499).
+constexpr int kDeepSteps = 16;
+
+template <typename T, int kBuf, bool SUB = false>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kBuf == 2 ? 3 : 2))) void k_offdiag(
     int n_unit, XcdRanges xr, const int32_t* __restrict__ unit_rng, const int32_t* __restrict__ unit_dst,
     const int32_t* __restrict__ trip, const T* __restrict__ R, double* __restrict__ blk, double* __restrict__ pblk) {
     constexpr int kVal = 16 / sizeof(T);                             // values per 16-byte chunk
     constexpr int kCh = kRec / kVal;                                 // chunks per record (12 or 6)
     constexpr int kCpl = 4 * kPairWave;                              // couples per step
     constexpr int kLoads = kCpl * 2 * kCh / kWave;                   // chunk copies per lane per step
-    constexpr int kRow = kCpl * kVal;                                // values per chunk slot row
     static_assert(kCpl == 16 && kLoads * kWave == kCpl * 2 * kCh, "staging must tile the wave");
-    __shared__ __align__(16) T sC[2][2 * kCh * kRow];
-    __shared__ int2 sT[2][kCpl];
+    static_assert(kBuf == 2 || kBuf == 3, "two or three buffers");
+    constexpr int kBufV = kLoads * kWave * kVal;
+    __shared__ __align__(16) T sC0[kBufV];
+    __shared__ __align__(16) T sC1[kBufV];
+    __shared__ __align__(16) T sC2[kBuf > 2 ? kBufV : 1];
     const int xcd = blockIdx.x % 8;
     const int wv = xr.wv[xcd] + (int)(blockIdx.x / 8);
     if (wv >= xr.wv[xcd + 1]) return;   // whole workgroup (one wave) leaves
@@ -347,40 +368,48 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3))) void
     int steps = (t1 - t0 + 3) / 4;
     steps = max(steps, __shfl_xor(steps, 16, kWave));
     steps = max(steps, __shfl_xor(steps, 32, kWave));
-    // couple (a, b) of step st for this lane's slot; (-1, -1) past the unit's end
+    steps = __builtin_amdgcn_readfirstlane(steps);
+    // this lane's couple of step st (past the unit's end: its last one)
     auto couple = [&](int st) {
-        const int t = t0 + 4 * st + slot;
-        return (st < steps && t < t1) ? reinterpret_cast<const int2*>(trip)[t] : make_int2(-1, -1);
+        return reinterpret_cast<const int2*>(trip)[max(0, min(t0 + 4 * st + slot, t1 - 1))];
     };
-    // copy k of the wave fills slots k * 64 .. k * 64 + 63: lane L moves
-    // chunk 4 k + L / 16 of couple L % 16 (chunks past kCh: the b record's)
-    auto issue = [&](int b) {
-        const int2 ab = sT[b][lane % kCpl];
+    // copy k of the wave fills its slots k * 64 .. k * 64 + 63: lane L moves
+    // chunk 4 k + (L % 4 ^ L / 16) of couple L / 4, its own (chunks past kCh: the b record's)
+    const int q4 = quarter ^ grp;
+    auto issue = [&](T* dst, int2 ab) {
+        const char* pa = reinterpret_cast<const char*>(R) + (int64_t)ab.x * (kRec * (int)sizeof(T));
+        const char* pb = reinterpret_cast<const char*>(R) + (int64_t)ab.y * (kRec * (int)sizeof(T));
 #pragma unroll
         for (int k = 0; k < kLoads; ++k) {
-            const int h = 4 * k + lane / kCpl;
-            const int o = h < kCh ? ab.x : ab.y;
-            const T* src = o >= 0 ? R + (int64_t)o * kRec + (h % kCh) * kVal : R;   // unused couple: any valid chunk
-            __builtin_amdgcn_global_load_lds((const void*)src,
-                                             (__attribute__((address_space(3))) void*)(sC[b] + k * kWave * kVal), 16,
-                                             0, 0);
+            const int h = 4 * k + q4;
+            const char* src = 4 * k + 3 < kCh ? pa + h * 16
+                              : 4 * k >= kCh ? pb + (h - kCh) * 16
+                                             : (h < kCh ? pa + h * 16 : pb + (h - kCh) * 16);
+            __builtin_amdgcn_global_load_lds((const void*)src, (__attribute__((address_space(3))) void*)(dst + k * kWave * kVal),
+                                             16, 0, 0);
         }
     };
     double acc[27];
 #pragma unroll
     for (int m = 0; m < 27; ++m) acc[m] = 0.0;
-    if (quarter == 0) { sT[0][cpl] = couple(0); sT[1][cpl] = couple(1); }
-    __syncthreads();
-    if (steps > 0) issue(0);
-    for (int st = 0; st < steps; ++st) {
-        const int b = st & 1;
-        const int2 nxt = quarter == 0 ? couple(st + 2) : make_int2(-1, -1);
-        __builtin_amdgcn_s_waitcnt(0);   // step st's records have landed in sC[b]
-        __syncthreads();
-        if (st + 1 < steps) issue(b ^ 1);
+    // One step: its records are in buf once at most the kBuf - 2 younger steps'
+    // copies are in flight; those of step st + kBuf - 1 go to nbuf.  With three
+    // buffers the copies past the last step (the units' last couples once
+    // more) are issued too: leaving them out would leave the number in flight
+    // open.
+    int2 nx[kBuf];
+    auto step = [&](const T* buf, T* nbuf, int2& nxt, int st) {
+        __builtin_amdgcn_s_waitcnt(0x0f70 | ((kBuf - 2) * kLoads));   // vmcnt only
+        if (kBuf > 2 || st + 1 < steps) {
+            issue(nbuf, nxt);
+            nxt = couple(st + 2 * kBuf - 1);
+        }
         // value v of this lane's couple (v < kRec: record a, else record b)
-        const T* me = sC[b] + cpl * kVal;
-        auto at = [&](int v) { return (double)me[(v / kVal) * kRow + v % kVal]; };
+        const T* me = buf + cpl * 4 * kVal;
+        auto at = [&](int v) {
+            const int h = v / kVal;
+            return (double)me[(h / 4) * (kWave * kVal) + ((h % 4) ^ grp) * kVal + v % kVal];
+        };
         const int t = t0 + 4 * st + slot;
         if (t < t1) {
             double ka[6], kb[6], jb0[3], jb1[3];
@@ -397,7 +426,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3))) void
             const double m10 = ka[3] * kb[0] + ka[4] * kb[1] + ka[5] * kb[2];
             double m11 = ka[3] * kb[3] + ka[4] * kb[4] + ka[5] * kb[5];
             if (SUB) {
-                const int2 ab = sT[b][cpl];
+                const int2 ab = reinterpret_cast<const int2*>(trip)[t];
                 if ((ab.x >> 1) == (ab.y >> 1)) { m00 -= 1.0; m11 -= 1.0; }
             }
             double p0[3], p1[3];
@@ -413,9 +442,30 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3))) void
                 for (int q = 0; q < 3; ++q) acc[r * 3 + q] += a0 * p0[q] + a1 * p1[q];
             }
         }
-        __syncthreads();   // every lane is done with sT[b] and sC[b]
-        if (quarter == 0) sT[b][cpl] = nxt;
+    };
+    {
+        int2 first[kBuf - 1];
+#pragma unroll
+        for (int k = 0; k < kBuf - 1; ++k) first[k] = couple(k);
+#pragma unroll
+        for (int k = 0; k < kBuf; ++k) nx[k] = couple(kBuf - 1 + k);
+        // these loads end here: left pending, the loop's first wait would be for everything
+#pragma unroll
+        for (int k = 0; k < kBuf; ++k) asm volatile("" : "+v"(nx[k].x), "+v"(nx[k].y));
+        issue(sC0, first[0]);
+        if constexpr (kBuf > 2) issue(sC1, first[1]);
     }
+    for (int st = 0; st < steps; st += kBuf) {
+        if constexpr (kBuf == 2) {
+            step(sC0, sC1, nx[0], st);
+            if (st + 1 < steps) step(sC1, sC0, nx[1], st + 1);
+        } else {
+            step(sC0, sC2, nx[0], st);
+            step(sC1, sC0, nx[1], st + 1);
+            step(sC2, sC1, nx[2], st + 2);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);   // no copy is on its way to LDS when the wave ends
 #pragma unroll
     for (int m = 0; m < 27; ++m) {
         acc[m] += __shfl_xor(acc[m], 4, kWave);
@@ -1012,14 +1062,17 @@ void launch_offdiag(ba_ctx* c) {
     for (int x = 0; x < 8; ++x) most = std::max(most, xr.wv[x + 1] - xr.wv[x]);
     const int grid = 8 * most;
     if (c->shared)
-        k_offdiag<double, true><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                               (const double*)c->R, c->blk, c->pblk);
+        k_offdiag<double, 2, true><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
+                                                                  (const double*)c->R, c->blk, c->pblk);
     else if (c->precision == BA_MIXED)
-        k_offdiag<float><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                        (const float*)c->R, c->blk, c->pblk);
+        k_offdiag<float, 2><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
+                                                           (const float*)c->R, c->blk, c->pblk);
+    else if (c->unit_steps >= (int64_t)kDeepSteps * c->n_unit)
+        k_offdiag<double, 3><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
+                                                            (const double*)c->R, c->blk, c->pblk);
     else
-        k_offdiag<double><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                         (const double*)c->R, c->blk, c->pblk);
+        k_offdiag<double, 2><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
+                                                            (const double*)c->R, c->blk, c->pblk);
     if (c->n_lseg > 0) {
         const int nl = c->n_lseg_long, ns = c->n_lseg - nl;
         const int64_t n = (int64_t)ns * 81;
