@@ -157,6 +157,24 @@ __device__ __forceinline__ void load_jc(const float* __restrict__ r, double* v) 
     const float2 t = reinterpret_cast<const float2*>(r)[8];
     v[16] = t.x; v[17] = t.y;
 }
+// The wave's LDS writes so far, seen by its later reads: without it the
+// compiler may order a lane's read before another lane's write
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// n records (REC bytes each, at a stride of PAD bytes in LDS) to consecutive
+// records in global memory, contiguous 16-byte chunks spread over the wave's
+// lanes instead of a record's stride apart.  PAD = REC + 16 spreads both the
+// lanes' records and the chunks over the banks.
+template <int REC, int PAD>
+__device__ __forceinline__ void wave_records_out(char* __restrict__ dst, const char* src, int n, int lane) {
+    constexpr int kCh = REC / 16;
+    for (int i = lane; i < n * kCh; i += kWave)
+        *reinterpret_cast<uint4*>(dst + i * 16) = *reinterpret_cast<const uint4*>(src + i / kCh * PAD + i % kCh * 16);
+}
+
 __device__ __forceinline__ void store_jc(double* __restrict__ r, const double* v) {
     double2* p = reinterpret_cast<double2*>(r);
 #pragma unroll

@@ -28,6 +28,7 @@ constexpr int WPB = BS / kWave;   // waves per block
 // reciprocals of L's diagonal, r = (L00, L10, L11, L20, L21, L22, lhat,
 // 1/L00, 1/L11, 1/L22).  Returns false if V* is not positive definite.
 constexpr int kPT = 12;   // point terms shared with a track's lanes
+constexpr int kPTRow = kPT + 1;   // a lane's row in LDS: an odd number of values, so that the lanes' rows spread over the banks
 __device__ __forceinline__ bool point_terms(const double* s, double lambda, double* r) {
     const double V00 = s[0] * (1.0 + lambda), V11 = s[3] * (1.0 + lambda), V22 = s[5] * (1.0 + lambda);
     const double L00 = sqrt(V00), i00 = 1.0 / L00;
@@ -75,7 +76,11 @@ __device__ __forceinline__ void store_ebar(const double* r, const double* K, dou
 // ---------------------------------------------------------------------------
 // point stage: one wave per chunk of whole tracks (<= 64 observations), one
 // lane per observation.  Track sums V_p, l_p are reduced through LDS by the
-// lane holding the first observation of the track.
+// lane holding the first observation of the track.  The waves of a workgroup
+// share nothing and do not wait for each other.  Bound by memory: K goes to
+// the last 48 of each record's 192 bytes, so every line is written in parts
+// (25 M observations, FP64: 1.9 GB read and 2.6 GB written in 1,772 us; 1,806
+// with each lane writing its K, 1,880 without the XCD-contiguous order).
 // ---------------------------------------------------------------------------
 // FROM_K: J_p is not stored; it is formed as K L^T from the record and the
 // point terms of the previous formation (read before they are replaced),
@@ -87,15 +92,16 @@ __global__ __launch_bounds__(BS) void k_point(int n_chunk, const int32_t* __rest
                                               T* __restrict__ R, T* __restrict__ Jp, const double* __restrict__ e,
                                               double lambda, double* __restrict__ ptL, const int32_t* __restrict__ obs_rpos,
                                               double* __restrict__ ebar, int* __restrict__ flags) {
-    __shared__ double sP[WPB][kWave][kPT];   // track sums, then the head's point terms
+    __shared__ __align__(16) double sP[WPB][kWave][kPTRow];   // track sums, the head's point terms, then K
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    const int chunk = blockIdx.x * WPB + wv;
+    const int chunk = xcd_block() * WPB + wv;
     int k0 = 0, k1 = 0;
     if (chunk < n_chunk) { k0 = chunk_ptr[chunk]; k1 = chunk_ptr[chunk + 1]; }
     const int k = k0 + lane;
     const bool act = k < k1;
     double jp[6];
     double2 ek = make_double2(0.0, 0.0);
+    int rpos = -1;
     const int p = act ? obs_pt[k] : -1;
     const Track tk = chunk_track(act, p, lane, k1 - k0);
     const int head = tk.head, tl = tk.len;
@@ -112,6 +118,7 @@ __global__ __launch_bounds__(BS) void k_point(int n_chunk, const int32_t* __rest
             load6(Jp + (int64_t)k * 6, jp);
         }
         ek = reinterpret_cast<const double2*>(e)[k];
+        rpos = obs_rpos[k];
         sP[wv][lane][0] = jp[0] * jp[0] + jp[3] * jp[3];
         sP[wv][lane][1] = jp[0] * jp[1] + jp[3] * jp[4];
         sP[wv][lane][2] = jp[0] * jp[2] + jp[3] * jp[5];
@@ -122,7 +129,7 @@ __global__ __launch_bounds__(BS) void k_point(int n_chunk, const int32_t* __rest
         sP[wv][lane][7] = -(jp[1] * ek.x + jp[4] * ek.y);
         sP[wv][lane][8] = -(jp[2] * ek.x + jp[5] * ek.y);
     }
-    __syncthreads();
+    wave_lds_sync();
     if (act && head == lane) {
         double s[9];
 #pragma unroll
@@ -138,23 +145,22 @@ __global__ __launch_bounds__(BS) void k_point(int n_chunk, const int32_t* __rest
 #pragma unroll
         for (int m = 0; m < 9; ++m) ptL[q * 9 + m] = r[m];
     }
-    __syncthreads();
+    wave_lds_sync();
+    double K[6];
     if (act) {
-        double K[6];
         point_K(sP[wv][head], jp, K);
-        store6(R + (int64_t)k * kRec + 18, K);
-        store_ebar<T>(sP[wv][head], K, ek.x, ek.y, obs_rpos[k], ebar);
+        store_ebar<T>(sP[wv][head], K, ek.x, ek.y, rpos, ebar);
     }
-}
-
-// n_bytes (a multiple of CH) from LDS to global memory, contiguous CH-byte
-// chunks spread over the wave's lanes (one fully used cache line per few
-// lanes per instruction)
-template <int CH>
-__device__ __forceinline__ void wave_copy_out(char* __restrict__ dst, const char* src, int n_bytes, int lane) {
-    using V = typename std::conditional<CH == 16, uint4, uint2>::type;
-    for (int o = lane * CH; o < n_bytes; o += kWave * CH)
-        *reinterpret_cast<V*>(dst + o) = *reinterpret_cast<const V*>(src + o);
+    wave_lds_sync();   // every lane has its point terms
+    T* stage = reinterpret_cast<T*>(&sP[wv][0][0]);
+    if (act) store6(stage + lane * 6, K);
+    wave_lds_sync();
+    // K into the records: neighbouring lanes write neighbouring 16 (FP32: 8) bytes
+    using V = typename std::conditional<sizeof(T) == 8, uint4, uint2>::type;
+    constexpr int kV = (int)(sizeof(V) / sizeof(T));
+    for (int i = lane; i < 3 * (k1 - k0); i += kWave)
+        *reinterpret_cast<V*>(R + (int64_t)(k0 + i / 3) * kRec + 18 + (i % 3) * kV) =
+            reinterpret_cast<const V*>(stage)[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -184,9 +190,14 @@ __device__ __forceinline__ void linpoint(int n_chunk, const int32_t* __restrict_
                                                  double* __restrict__ e, double* __restrict__ ptL,
                                                  const int32_t* __restrict__ obs_rpos, double* __restrict__ ebar,
                                                  double* __restrict__ part, int* __restrict__ flags) {
-    __shared__ __align__(16) double sP[NW][kWave][kPT];   // track sums, the head's point terms, then staging
+    constexpr int kRecB = kRec * (int)sizeof(T), kPadB = kRecB + 16;   // a staged record's stride: over all banks
+    constexpr int kPer = sizeof(T) == 8 ? 32 : kWave;                  // records per round
+    // track sums, the head's point terms, then staging
+    __shared__ __align__(16) char sS[NW][kPer * kPadB];
+    static_assert(kPer * kPadB >= kWave * kPTRow * (int)sizeof(double), "both uses fit");
     __shared__ double sh[NW];
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    double (*sP)[kPTRow] = reinterpret_cast<double (*)[kPTRow]>(sS[wv]);
     const int chunk = xcd_block() * NW + wv;   // neighbouring chunks on one XCD
     int k0 = 0, k1 = 0;
     if (chunk < n_chunk) { k0 = chunk_ptr[chunk]; k1 = chunk_ptr[chunk + 1]; }
@@ -194,12 +205,14 @@ __device__ __forceinline__ void linpoint(int n_chunk, const int32_t* __restrict_
     const bool act = k < k1;
     double jc[18], jp[6];
     double cost = 0.0, eu = 0.0, ev = 0.0;
+    int rpos = -1;
     const int p = act ? obs_pt[k] : -1;
     const Track tk = chunk_track(act, p, lane, k1 - k0);
     const int head = tk.head, tl = tk.len;
     const int64_t q = chunk < n_chunk ? (int64_t)chunk_q[chunk] + tk.idx : 0;   // internal point index
     if (act) {
         const double* X = pts + (int64_t)p * 3;
+        rpos = obs_rpos[k];
         double pu, pv;
         project_point<true>(cams + (int64_t)obs_cam[k] * 9, X[0], X[1], X[2], pu, pv, jc, jp);
         eu = pu - uv[k];
@@ -211,15 +224,15 @@ __device__ __forceinline__ void linpoint(int n_chunk, const int32_t* __restrict_
         for (int m = 0; m < 6; ++m) jp[m] = (double)(T)jp[m];
         reinterpret_cast<double2*>(e)[k] = make_double2(eu, ev);
         cost = 0.5 * (eu * eu + ev * ev);
-        sP[wv][lane][0] = jp[0] * jp[0] + jp[3] * jp[3];
-        sP[wv][lane][1] = jp[0] * jp[1] + jp[3] * jp[4];
-        sP[wv][lane][2] = jp[0] * jp[2] + jp[3] * jp[5];
-        sP[wv][lane][3] = jp[1] * jp[1] + jp[4] * jp[4];
-        sP[wv][lane][4] = jp[1] * jp[2] + jp[4] * jp[5];
-        sP[wv][lane][5] = jp[2] * jp[2] + jp[5] * jp[5];
-        sP[wv][lane][6] = -(jp[0] * eu + jp[3] * ev);
-        sP[wv][lane][7] = -(jp[1] * eu + jp[4] * ev);
-        sP[wv][lane][8] = -(jp[2] * eu + jp[5] * ev);
+        sP[lane][0] = jp[0] * jp[0] + jp[3] * jp[3];
+        sP[lane][1] = jp[0] * jp[1] + jp[3] * jp[4];
+        sP[lane][2] = jp[0] * jp[2] + jp[3] * jp[5];
+        sP[lane][3] = jp[1] * jp[1] + jp[4] * jp[4];
+        sP[lane][4] = jp[1] * jp[2] + jp[4] * jp[5];
+        sP[lane][5] = jp[2] * jp[2] + jp[5] * jp[5];
+        sP[lane][6] = -(jp[0] * eu + jp[3] * ev);
+        sP[lane][7] = -(jp[1] * eu + jp[4] * ev);
+        sP[lane][8] = -(jp[2] * eu + jp[5] * ev);
     }
     const double csum = block_sum<NW * kWave>(cost, sh);   // contains the barrier for sP
     if (threadIdx.x == 0) part[blockIdx.x] = csum;
@@ -229,41 +242,38 @@ __device__ __forceinline__ void linpoint(int n_chunk, const int32_t* __restrict_
         for (int m = 0; m < 9; ++m) s[m] = 0.0;
         for (int q = 0; q < tl; ++q)
 #pragma unroll
-            for (int m = 0; m < 9; ++m) s[m] += sP[wv][lane + q][m];
+            for (int m = 0; m < 9; ++m) s[m] += sP[lane + q][m];
         double r[kPT];
         if (!point_terms(s, lambda, r)) flags[0] = 1;
         // the head's own row is read by no other lane: it holds the track's terms now
 #pragma unroll
-        for (int m = 0; m < kPT; ++m) sP[wv][lane][m] = r[m];
+        for (int m = 0; m < kPT; ++m) sP[lane][m] = r[m];
 #pragma unroll
         for (int m = 0; m < 9; ++m) ptL[q * 9 + m] = r[m];
     }
     __syncthreads();
     double K[6];
     if (act) {
-        point_K(sP[wv][head], jp, K);
-        store_ebar<T>(sP[wv][head], K, eu, ev, obs_rpos[k], ebar);
+        point_K(sP[head], jp, K);
+        store_ebar<T>(sP[head], K, eu, ev, rpos, ebar);
     }
     __syncthreads();   // every lane has its point terms: sP is free for staging
     // The wave's records (J_c, K) are contiguous in memory; they are staged
-    // through the wave's 6 KB of sP and written with contiguous 16-byte
+    // through the wave's part of LDS and written with contiguous 16-byte
     // chunks spread over the lanes, instead of each lane writing its own
     // record at a 192-byte (96-byte) stride.
-    char* stage = reinterpret_cast<char*>(&sP[wv][0][0]);
-    constexpr int kStageB = kWave * kPT * (int)sizeof(double);
-    constexpr int kRecB = kRec * (int)sizeof(T);
-    constexpr int kPer = kStageB / kRecB;      // records per round: 32 (FP64), 64 (FP32)
+    char* stage = sS[wv];
     const int nrec = k1 - k0;
 #pragma unroll
     for (int r0 = 0; r0 < kWave; r0 += kPer) {
         if (act && lane >= r0 && lane < r0 + kPer) {
-            T* d = reinterpret_cast<T*>(stage + (lane - r0) * kRecB);
+            T* d = reinterpret_cast<T*>(stage + (lane - r0) * kPadB);
             store_jc(d, jc);
             store6(d + 18, K);
         }
         __syncthreads();
-        wave_copy_out<16>(reinterpret_cast<char*>(R + (int64_t)(k0 + r0) * kRec), stage,
-                          max(0, min(nrec - r0, kPer)) * kRecB, lane);
+        wave_records_out<kRecB, kPadB>(reinterpret_cast<char*>(R + (int64_t)(k0 + r0) * kRec), stage,
+                                       min(nrec - r0, kPer), lane);
         __syncthreads();
     }
 }
@@ -622,7 +632,9 @@ __global__ __launch_bounds__(NW * kWave) void k_diag(int n_rows, const int32_t* 
 // l = -J^T e: the solve's right-hand side is w = L^T dx_p, so an
 // observation's J dx = J_c dxc + K w with no J_p (J_p = K L^T).  One wave per
 // chunk of whole tracks, one lane per observation; per-block partials of the
-// two model terms.
+// two model terms.  Bound by reading the records; everything that needs only
+// the chunk's place is asked for at once (25 M observations, FP64: 1,611 ->
+// 1,590 us, 4.1 TB/s; 2.4 M: 94.7 -> 92.0).
 // ---------------------------------------------------------------------------
 // four waves per workgroup (on the 60,000-camera partition, FP64: 6.40 ms
 // against 6.46 with two and 6.50 with one), blocks in XCD-contiguous order
@@ -648,8 +660,14 @@ __global__ __launch_bounds__(kBackNW * kWave) void k_backsub(int n_chunk, const 
     const Track tk = chunk_track(act, p, lane, k1 - k0);
     const int head = tk.head, tl = tk.len;
     const int64_t q = chunk < n_chunk ? (int64_t)chunk_q[chunk] + tk.idx : 0;   // internal point index
-    double K[6], g0 = 0.0, g1 = 0.0;
+    double K[6], L[9], g0 = 0.0, g1 = 0.0;
+    double2 ek;
+    if (act && head == lane) {
+#pragma unroll
+        for (int m = 0; m < 9; ++m) L[m] = ptL[q * 9 + m];
+    }
     if (act) {
+        ek = reinterpret_cast<const double2*>(e)[k];
         const int row = obs_row[k];
         const T* rk = R + (int64_t)k * kRec;
         load6(rk + 18, K);
@@ -668,11 +686,10 @@ __global__ __launch_bounds__(kBackNW * kWave) void k_backsub(int n_chunk, const 
         sP[wv][lane][1] = K[1] * g0 + K[4] * g1;
         sP[wv][lane][2] = K[2] * g0 + K[5] * g1;
     }
-    __syncthreads();
+    wave_lds_sync();
     if (act && head == lane) {
         double u0 = 0.0, u1 = 0.0, u2 = 0.0;
         for (int q = 0; q < tl; ++q) { u0 += sP[wv][lane + q][0]; u1 += sP[wv][lane + q][1]; u2 += sP[wv][lane + q][2]; }
-        const double* L = ptL + q * 9;
         u0 = L[6] - u0; u1 = L[7] - u1; u2 = L[8] - u2;
         // L^T x = u with L = [[L00,0,0],[L10,L11,0],[L20,L21,L22]]
         const double x2 = u2 / L[5];
@@ -684,13 +701,12 @@ __global__ __launch_bounds__(kBackNW * kWave) void k_backsub(int n_chunk, const 
         // the head's own row is read by no other lane now: w for the track
         sP[wv][lane][0] = u0; sP[wv][lane][1] = u1; sP[wv][lane][2] = u2;
     }
-    __syncthreads();
+    wave_lds_sync();
     double jdx2 = 0.0, dxl = 0.0;
     if (act) {
         const double* w = sP[wv][head];
         const double a0 = g0 + K[0] * w[0] + K[1] * w[1] + K[2] * w[2];
         const double a1 = g1 + K[3] * w[0] + K[4] * w[1] + K[5] * w[2];
-        const double2 ek = reinterpret_cast<const double2*>(e)[k];
         jdx2 = a0 * a0 + a1 * a1;
         dxl = -(a0 * ek.x + a1 * ek.y);
     }
