@@ -73,6 +73,7 @@ void free_ctx(ba_ctx* c) {
         if (p) (void)hipFree(p);
     if (c->h_scal) (void)hipHostFree(c->h_scal);
     if (c->h_flags) (void)hipHostFree(c->h_flags);
+    if (c->h_stamp) (void)hipHostFree(c->h_stamp);
     for (auto& e : c->ev)
         if (e) (void)hipEventDestroy(e);
     for (auto& g : c->pcg_graphs) (void)hipGraphExecDestroy(g.exec);
@@ -720,6 +721,13 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     dalloc(c, &P.scal, 8);
     BA_HIP_CHECK(hipHostMalloc((void**)&c->h_scal, 32 * sizeof(double), hipHostMallocDefault));
     BA_HIP_CHECK(hipHostMalloc((void**)&c->h_flags, 16 * sizeof(int), hipHostMallocDefault));
+    BA_HIP_CHECK(hipHostMalloc((void**)&c->h_stamp, ba::kStCount * sizeof(ba::u64), hipHostMallocDefault));
+    std::memset(c->h_stamp, 0, ba::kStCount * sizeof(ba::u64));
+    {
+        int khz = 0;
+        BA_HIP_CHECK(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, c->device));
+        c->stamp_ms = khz > 0 ? 1.0 / khz : 0.0;
+    }
     for (auto& e : c->ev) BA_HIP_CHECK(hipEventCreate(&e));
     BA_HIP_CHECK(hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
     if (const char* g = std::getenv("BA_PCG_GRAPHS")) c->use_graphs = std::atoi(g) != 0;
@@ -770,34 +778,35 @@ ba_status guarded(ba_ctx* c, F&& f) {
     }
 }
 
-float elapsed(hipEvent_t a, hipEvent_t b) {
-    float ms = 0.f;
-    if (hipEventElapsedTime(&ms, a, b) != hipSuccess) return 0.f;
-    return ms;
+// milliseconds between two stamps of finished work
+double elapsed(const ba_ctx* c, int a, int b) {
+    const ba::u64 t0 = c->h_stamp[a], t1 = c->h_stamp[b];
+    return t1 > t0 ? (double)(t1 - t0) * c->stamp_ms : 0.0;
 }
 
-// point_done: the point stage already ran, fused with the linearization
-ba_status form_rcs_async(ba_ctx* c, double lambda, bool point_done = false) {
+// point_done: the point stage already ran, fused with the linearization, which
+// ended at stamp kStLinEnd.  end: the stamp that the caller lets follow.
+ba_status form_rcs_async(ba_ctx* c, double lambda, bool point_done, int end) {
+    int begin = ba::kStLinEnd, pair = ba::kStLinEnd;
     if (!point_done) {
         // flags[2] (records out of range) belongs to the linearization and stays
-        BA_HIP_CHECK(hipMemsetAsync(c->flags, 0, 2 * sizeof(int), c->stream));
-        BA_HIP_CHECK(hipMemsetAsync(c->flags + 3, 0, 5 * sizeof(int), c->stream));
-    }
-    BA_HIP_CHECK(hipEventRecord(c->ev[1], c->stream));
-    if (!point_done) {
+        begin = ba::kStForm;
+        pair = ba::kStPair;
+        ba::launch_begin(c, 0xfb, {}, {}, begin);
         if (c->shared)   // the point terms need the Jacobians again: one fused pass
-            ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, lambda);
+            ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, lambda, nullptr);
         else
             ba::launch_point(c, lambda);
     }
-    BA_HIP_CHECK(hipEventRecord(c->ev[2], c->stream));
-    ba::launch_offdiag(c);
-    BA_HIP_CHECK(hipEventRecord(c->ev[3], c->stream));
-    if (c->shared)
+    ba::launch_offdiag(c, point_done ? nullptr : c->h_stamp + pair);
+    if (c->shared) {
+        ba::launch_stamp(c, ba::kStDiag);
         ba::launch_node_diag(c, lambda);
-    else
-        ba::launch_diag(c, lambda);
-    BA_HIP_CHECK(hipEventRecord(c->ev[4], c->stream));
+    } else {
+        ba::launch_diag(c, lambda, c->h_stamp + ba::kStDiag);
+    }
+    const int span[3][2] = {{begin, pair}, {pair, ba::kStDiag}, {ba::kStDiag, end}};
+    std::memcpy(c->st_span[1], span, sizeof span);
     BA_HIP_CHECK(hipGetLastError());
     c->have_rcs = true;
     c->sf_ready = false;
@@ -1237,23 +1246,19 @@ ba_status ba_linearize(ba_ctx* c, const double* cams, const double* pts, double*
     if (!c) return BA_ERR_INVALID_ARG;
     if (!cams || !pts) { c->err = "null parameter arrays"; return BA_ERR_INVALID_ARG; }
     return guarded(c, [&]() {
-        BA_HIP_CHECK(hipEventRecord(c->ev[0], c->stream));
-        BA_HIP_CHECK(hipMemsetAsync(c->flags + 2, 0, sizeof(int), c->stream));
         if (c->shared) {
             // the Jacobians are formed again with the damping by ba_form_rcs
             // (one fused pass); the parameters are kept for it
-            BA_HIP_CHECK(hipMemcpyAsync(c->lin_params, cams, n_params(c) * sizeof(double), hipMemcpyDeviceToDevice,
-                                        c->stream));
-            BA_HIP_CHECK(hipMemcpyAsync(c->lin_pts, pts, (size_t)c->n_pts * 3 * sizeof(double),
-                                        hipMemcpyDeviceToDevice, c->stream));
-            ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, 0.0);
+            ba::launch_begin(c, 4, {c->lin_params, cams, (int64_t)n_params(c)}, {c->lin_pts, pts, 3 * (int64_t)c->n_pts},
+                             ba::kStLin);
+            ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, 0.0, c->h_stamp + ba::kStLinEnd);
         } else {
-            ba::launch_linearize(c, cams, pts);
-            BA_HIP_CHECK(hipMemcpyAsync(c->lin_cams, cams, (size_t)c->n_cams * 9 * sizeof(double),
-                                        hipMemcpyDeviceToDevice, c->stream));
+            ba::launch_begin(c, 4, {c->lin_cams, cams, 9 * (int64_t)c->n_cams}, {}, ba::kStLin);
+            ba::launch_linearize(c, cams, pts, c->h_stamp + ba::kStLinEnd);
         }
+        c->st_span[0][0] = ba::kStLin;
+        c->st_span[0][1] = ba::kStLinEnd;
         c->defl_ready = false;
-        BA_HIP_CHECK(hipEventRecord(c->ev[5], c->stream));
         BA_HIP_CHECK(hipGetLastError());
         c->have_lin = true;
         c->have_rcs = false;
@@ -1273,7 +1278,8 @@ ba_status ba_form_rcs(ba_ctx* c, double lambda) {
     if (!c->have_lin) { c->err = "ba_form_rcs needs a prior ba_linearize"; return BA_ERR_STATE; }
     if (!(lambda >= 0.0) || !std::isfinite(lambda)) { c->err = "lambda must be finite and >= 0"; return BA_ERR_INVALID_ARG; }
     return guarded(c, [&]() {
-        form_rcs_async(c, lambda);
+        form_rcs_async(c, lambda, false, ba::kStPrep);
+        ba::launch_stamp(c, ba::kStPrep);
         BA_HIP_CHECK(hipMemcpyAsync(c->h_flags, c->flags, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
         BA_HIP_CHECK(hipStreamSynchronize(c->stream));
         if (c->h_flags[2]) { c->err = kRangeMsg; return BA_ERR_RANGE; }
@@ -1287,10 +1293,7 @@ ba_status ba_get_stage_ms(ba_ctx* c, double* ms) {
     if (!c || !ms) return BA_ERR_INVALID_ARG;
     return guarded(c, [&]() {
         BA_HIP_CHECK(hipStreamSynchronize(c->stream));
-        ms[0] = elapsed(c->ev[0], c->ev[5]);
-        ms[1] = elapsed(c->ev[1], c->ev[2]);
-        ms[2] = elapsed(c->ev[2], c->ev[3]);
-        ms[3] = elapsed(c->ev[3], c->ev[4]);
+        for (int i = 0; i < 4; ++i) ms[i] = elapsed(c, c->st_span[i][0], c->st_span[i][1]);
         return BA_OK;
     });
 }
@@ -1330,7 +1333,7 @@ ba_status ba_pcg_solve(ba_ctx* c, const ba_pcg_opts* o, double* dxc, ba_pcg_info
         if (pre == BA_PRECOND_LEARNED_FSAI && c->n_rows > 0) prepare_learned_fsai(c);
         const int defl = (o && o->deflate && c->n_rows > 0) ? 1 : 0;
         if (defl) prepare_defl(c);
-        BA_HIP_CHECK(hipEventRecord(c->ev[6], c->stream));
+        ba::launch_stamp(c, ba::kStSolve);
         ba_status s = BA_OK;
         int fell_back = 0;
         if (c->n_rows > 0) {
@@ -1341,13 +1344,15 @@ ba_status ba_pcg_solve(ba_ctx* c, const ba_pcg_opts* o, double* dxc, ba_pcg_info
                 s = ba::run_pcg(c, 0, c->Minv, defl, tol, max_iter, o ? o->x0 : nullptr, dxc, &it, &rr);
             }
         }
-        BA_HIP_CHECK(hipEventRecord(c->ev[7], c->stream));
-        BA_HIP_CHECK(hipEventSynchronize(c->ev[7]));
+        if (c->n_rows == 0) {   // a solve has waited for its end
+            ba::launch_stamp(c, ba::kStBack);
+            BA_HIP_CHECK(hipStreamSynchronize(c->stream));
+        }
         if (info) {
             info->iters = it;
             info->status = s;
             info->relres = rr;
-            info->ms = elapsed(c->ev[6], c->ev[7]);
+            info->ms = elapsed(c, ba::kStSolve, ba::kStBack);
             info->precond_fallback = fell_back;
             info->reserved = 0;
         }
@@ -1428,78 +1433,101 @@ ba_status ba_lm_step(ba_ctx* c, double* cams, double* pts, ba_lm_state* st, cons
     return guarded(c, [&]() {
         ba_lm_info I;
         std::memset(&I, 0, sizeof I);
-        hipEvent_t* ev = c->ev;
-        BA_HIP_CHECK(hipEventRecord(ev[8], c->stream));
         const bool relin = !(st->flags & 1) || !c->have_lin;
-        BA_HIP_CHECK(hipEventRecord(ev[0], c->stream));
         if (relin) {
             // linearization and point stage in one pass (the records are written whole)
-            BA_HIP_CHECK(hipMemsetAsync(c->flags, 0, 8 * sizeof(int), c->stream));
             if (c->shared) {
-                BA_HIP_CHECK(hipMemcpyAsync(c->lin_params, cams, n_params(c) * sizeof(double),
-                                            hipMemcpyDeviceToDevice, c->stream));
-                BA_HIP_CHECK(hipMemcpyAsync(c->lin_pts, pts, (size_t)c->n_pts * 3 * sizeof(double),
-                                            hipMemcpyDeviceToDevice, c->stream));
-                ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, st->lambda);
+                ba::launch_begin(c, 0xff, {c->lin_params, cams, (int64_t)n_params(c)},
+                                 {c->lin_pts, pts, 3 * (int64_t)c->n_pts}, ba::kStLin);
+                ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, st->lambda, c->h_stamp + ba::kStLinEnd);
             } else {
-                ba::launch_linearize_point(c, cams, pts, st->lambda);
-                BA_HIP_CHECK(hipMemcpyAsync(c->lin_cams, cams, (size_t)c->n_cams * 9 * sizeof(double),
-                                            hipMemcpyDeviceToDevice, c->stream));
+                ba::launch_begin(c, 0xff, {c->lin_cams, cams, 9 * (int64_t)c->n_cams}, {}, ba::kStLin);
+                ba::launch_linearize_point(c, cams, pts, st->lambda, c->h_stamp + ba::kStLinEnd);
             }
+            c->st_span[0][0] = ba::kStLin;
+            c->st_span[0][1] = ba::kStLinEnd;
             c->defl_ready = false;
+        } else {
+            c->st_span[0][0] = c->st_span[0][1] = ba::kStForm;   // no linearization
         }
-        BA_HIP_CHECK(hipEventRecord(ev[5], c->stream));
         c->have_lin = true;
-        form_rcs_async(c, st->lambda, relin);
+        form_rcs_async(c, st->lambda, relin, ba::kStPrep);
         int it = 0;
         double rr = 0.0;
         ba_status ps = BA_OK;
-        BA_HIP_CHECK(hipEventRecord(ev[14], c->stream));
         select_solver_matrix(c, o ? o->solver_fp32 : 0, o ? o->product : BA_PRODUCT_AUTO,
                              pre == BA_PRECOND_FSAI || pre == BA_PRECOND_LEARNED_FSAI);
-        if (pre == BA_PRECOND_LEARNED && c->n_rows > 0) prepare_learned(c);
-        if (pre == BA_PRECOND_FSAI && c->n_rows > 0) prepare_fsai(c);
-        if (pre == BA_PRECOND_LEARNED_FSAI && c->n_rows > 0) prepare_learned_fsai(c);
         const int defl = (o && o->deflate && c->n_rows > 0) ? 1 : 0;
-        if (defl) prepare_defl(c);
-        BA_HIP_CHECK(hipEventRecord(ev[6], c->stream));
-        if (c->n_rows > 0) {
-            ps = ba::run_pcg(c, (pre == BA_PRECOND_FSAI || pre == BA_PRECOND_LEARNED_FSAI) ? 1 : 0, pre == BA_PRECOND_LEARNED ? c->Mlearn : c->Minv, defl,
-                             tol, max_iter, nullptr, c->dxc, &it, &rr);
-            if (learned_failed(pre, ps, rr)) {
+        // without a preparation the solve's own first kernel ends the formation
+        const bool plain = pre == BA_PRECOND_BLOCK_JACOBI && !defl && c->n_rows > 0;
+        if (!plain) {
+            ba::launch_stamp(c, ba::kStPrep);
+            if (pre == BA_PRECOND_LEARNED && c->n_rows > 0) prepare_learned(c);
+            if (pre == BA_PRECOND_FSAI && c->n_rows > 0) prepare_fsai(c);
+            if (pre == BA_PRECOND_LEARNED_FSAI && c->n_rows > 0) prepare_learned_fsai(c);
+            if (defl) prepare_defl(c);
+            ba::launch_stamp(c, ba::kStSolve);
+        }
+        const int n_tri = o ? o->retriangulate : 0;
+        // Solve, back-substitution, cost and update are enqueued without a wait
+        // where the solve is one kernel and needs no look at its outcome; the
+        // host waits once, for the step's end.
+        const bool look = pre == BA_PRECOND_LEARNED || pre == BA_PRECOND_LEARNED_FSAI;
+        auto solve = [&](bool wait) {
+            if (c->n_rows == 0) {
+                BA_HIP_CHECK(hipMemsetAsync(c->dxc, 0, sizeof(double), c->stream));
+                ba::launch_stamp(c, ba::kStBack);
+                return;
+            }
+            ps = ba::run_pcg(c, (pre == BA_PRECOND_FSAI || pre == BA_PRECOND_LEARNED_FSAI) ? 1 : 0,
+                             pre == BA_PRECOND_LEARNED ? c->Mlearn : c->Minv, defl, tol, max_iter, nullptr, c->dxc, &it,
+                             &rr, wait, plain ? c->h_stamp + ba::kStPrep : nullptr);
+            if (look && learned_failed(pre, ps, rr)) {
                 // the network's preconditioner is not usable on this RCS (not
                 // SPD, or non-finite): solve again with block-Jacobi
                 I.precond_fallback = 1;
                 ps = ba::run_pcg(c, 0, c->Minv, defl, tol, max_iter, nullptr, c->dxc, &it, &rr);
             }
-        } else
-            BA_HIP_CHECK(hipMemsetAsync(c->dxc, 0, sizeof(double), c->stream));
-        BA_HIP_CHECK(hipEventRecord(ev[7], c->stream));
-        if (c->shared)
-            ba::launch_back_substitute_shared(c, c->dxc, c->dxp);
-        else
-            ba::launch_back_substitute(c, c->dxc, c->dxp);
-        const int n_tri = o ? o->retriangulate : 0;
-        if (n_tri > 0) {
-            // the points re-triangulated with the candidate cameras, starting
-            // from the back-substituted ones; dxp becomes their displacement
-            BA_HIP_CHECK(hipMemsetAsync(c->tri_failed, 0, sizeof(int), c->stream));
-            ba::launch_triangulate(c, cams, c->dxc, pts, c->dxp, 1, 0, n_tri, c->tri_failed);
-            ba::launch_model_terms(c, c->dxc, c->dxp);
-            BA_HIP_CHECK(hipMemcpyAsync(c->h_flags + 3, c->tri_failed, sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        } else {
-            c->h_flags[3] = 0;
+        };
+        auto finish = [&]() {
+            if (c->shared) {
+                ba::launch_back_substitute_shared(c, c->dxc, c->dxp);
+                ba::launch_stamp(c, ba::kStEval);
+            } else {
+                ba::launch_back_substitute(c, c->dxc, c->dxp, c->h_stamp + ba::kStEval);
+            }
+            if (n_tri > 0) {
+                // the points re-triangulated with the candidate cameras, starting
+                // from the back-substituted ones; dxp becomes their displacement
+                BA_HIP_CHECK(hipMemsetAsync(c->tri_failed, 0, sizeof(int), c->stream));
+                ba::launch_triangulate(c, cams, c->dxc, pts, c->dxp, 1, 0, n_tri, c->tri_failed);
+                ba::launch_model_terms(c, c->dxc, c->dxp, c->h_stamp + ba::kStEval);
+            }
+            const ba::StepEnd E{c->scal, c->pcg.scal, c->flags, c->pcg.state, n_tri > 0 ? c->tri_failed : nullptr,
+                                c->h_scal, c->h_flags, c->h_stamp + ba::kStEnd, it < 0 ? -1 : (int)ps};
+            if (c->shared) {
+                ba::launch_evaluate_shared(c, cams, pts, c->dxc, c->dxp, c->h_stamp + ba::kStUpdate);
+                ba::launch_update_shared(c, cams, pts, c->dxc, c->dxp, E);
+            } else {
+                ba::launch_evaluate(c, cams, pts, c->dxc, c->dxp, c->h_stamp + ba::kStUpdate);
+                ba::launch_update(c, cams, pts, c->dxc, c->dxp, E);
+            }
+            BA_HIP_CHECK(hipStreamSynchronize(c->stream));
+            BA_HIP_CHECK(hipGetLastError());
+        };
+        solve(look);
+        finish();
+        if (it < 0 && c->h_flags[8]) {
+            // not all workgroups of the solve ran at once, nothing was updated:
+            // this context solves with one kernel per phase from now on
+            c->chip.G = 0;
+            solve(true);
+            finish();
+        } else if (it < 0) {
+            it = c->h_flags[7];
+            rr = c->h_scal[9];
+            ps = (ba_status)c->h_flags[6];
         }
-        BA_HIP_CHECK(hipEventRecord(ev[9], c->stream));
-        if (c->shared)
-            ba::launch_evaluate_shared(c, cams, pts, c->dxc, c->dxp);
-        else
-            ba::launch_evaluate(c, cams, pts, c->dxc, c->dxp);
-        BA_HIP_CHECK(hipEventRecord(ev[10], c->stream));
-        BA_HIP_CHECK(hipMemcpyAsync(c->h_scal, c->scal, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        BA_HIP_CHECK(hipMemcpyAsync(c->h_flags, c->flags, 3 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-        BA_HIP_CHECK(hipStreamSynchronize(c->stream));
-        BA_HIP_CHECK(hipGetLastError());
         const double F = c->h_scal[0], Fn = c->h_scal[1], jdx2 = c->h_scal[2], dxl = c->h_scal[3];
         const double L = dxl - 0.5 * jdx2;
         I.cost = F;
@@ -1513,20 +1541,13 @@ ba_status ba_lm_step(ba_ctx* c, double* cams, double* pts, ba_lm_state* st, cons
         if (c->h_flags[2]) {
             // the linearization does not fit the records: no step is taken and
             // the state is left as it was
-            BA_HIP_CHECK(hipEventRecord(ev[11], c->stream));
-            BA_HIP_CHECK(hipEventSynchronize(ev[11]));
             if (info) *info = I;
             c->err = kRangeMsg;
             return BA_ERR_RANGE;
         }
         const bool formed = !c->h_flags[0] && !c->h_flags[1];
         if (!formed) I.pcg_status = BA_ERR_NOT_SPD;
-        const bool ok = formed && (ps == BA_OK || ps == BA_ERR_NOT_CONVERGED) && L > 0.0 && std::isfinite(Fn) && Fn < F;
-        if (ok) {
-            if (c->shared)
-                ba::launch_update_shared(c, cams, pts, c->dxc, c->dxp);
-            else
-                ba::launch_update(c, cams, pts, c->dxc, c->dxp);
+        if (c->h_flags[9]) {   // accepted on the device, the parameters are updated
             const double t = 2.0 * I.rho - 1.0;
             st->lambda *= std::max(1.0 / 3.0, 1.0 - t * t * t);
             st->nu = 2.0;
@@ -1539,15 +1560,13 @@ ba_status ba_lm_step(ba_ctx* c, double* cams, double* pts, ba_lm_state* st, cons
             st->flags |= 1;
         }
         st->iter += 1;
-        BA_HIP_CHECK(hipEventRecord(ev[11], c->stream));
-        BA_HIP_CHECK(hipEventSynchronize(ev[11]));
-        I.ms_linearize = elapsed(ev[0], ev[5]);
-        I.ms_form_rcs = elapsed(ev[1], ev[4]);
-        I.ms_pcg = elapsed(ev[6], ev[7]);
-        I.ms_back_substitute = elapsed(ev[7], ev[9]);
-        I.ms_evaluate = elapsed(ev[9], ev[10]);
-        I.ms_total = elapsed(ev[8], ev[11]);
-        I.ms_precond = (pre != BA_PRECOND_BLOCK_JACOBI || (o && o->deflate)) ? elapsed(ev[14], ev[6]) : 0.0;
+        I.ms_linearize = elapsed(c, c->st_span[0][0], c->st_span[0][1]);
+        I.ms_form_rcs = elapsed(c, c->st_span[1][0], ba::kStPrep);
+        I.ms_pcg = elapsed(c, plain ? ba::kStPrep : ba::kStSolve, ba::kStBack);
+        I.ms_back_substitute = elapsed(c, ba::kStBack, ba::kStEval);
+        I.ms_evaluate = elapsed(c, ba::kStEval, ba::kStUpdate);
+        I.ms_total = elapsed(c, relin ? ba::kStLin : ba::kStForm, ba::kStEnd);
+        I.ms_precond = (pre != BA_PRECOND_BLOCK_JACOBI || (o && o->deflate)) ? elapsed(c, ba::kStPrep, ba::kStSolve) : 0.0;
         if (info) *info = I;
         return BA_OK;
     });

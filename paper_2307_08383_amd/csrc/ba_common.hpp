@@ -304,6 +304,12 @@ __device__ __forceinline__ Track chunk_track(bool act, int p, int lane, int len)
     return t;
 }
 
+using u64 = unsigned long long;
+// the first block's start into *p (if given)
+__device__ __forceinline__ void stamp_now(u64* p) {
+    if (p && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *p = (u64)wall_clock64();
+}
+
 // Block index in XCD-contiguous order: the blocks that run on one XCD
 // (hardware block id mod 8) take one contiguous range of indices, so the
 // lines that neighbouring blocks share stay in that XCD's L2.
@@ -557,7 +563,14 @@ struct ba_ctx {
     ba::Fsai fs;
     ba::Csr csr;
     ba::Chip chip;
-    hipEvent_t ev[16] = {};
+    hipEvent_t ev[2] = {};             // the two batches of iterations in flight
+    // Time stamps of the stages (100 MHz clock), written to pinned memory by
+    // the stages' own kernels: an event in the stream between two kernels held
+    // the second up for 5 us, of which an LM step had 15.  Indices (kSt*); the
+    // begin and end of linearization, point, pair and diagonal stage last run
+    ba::u64* h_stamp = nullptr;
+    int st_span[4][2] = {};
+    double stamp_ms = 0.0;             // milliseconds a tick
     hipStream_t capture_stream = nullptr;
     bool use_graphs = true;
     struct PcgGraph {
@@ -602,30 +615,71 @@ namespace ba {
 // launchers (stream-ordered, no synchronisation)
 void launch_project(const double* cams, const double* pts, const int32_t* obs_cam, const int32_t* obs_pt,
                     int64_t n_obs, const double* noise, double* uv, hipStream_t st);
-void launch_linearize(ba_ctx* c, const double* cams, const double* pts);      // -> J, e, scal[0] = F
+// Stamps: kernels take the address of one and write it when their first block
+// starts (the end of a stage is the start of the next, or of a sum's last block)
+enum { kStLin = 0, kStLinEnd, kStForm, kStPair, kStDiag, kStPrep, kStSolve, kStBack, kStEval, kStUpdate, kStEnd, kStSpare, kStCount };
+void launch_stamp(ba_ctx* c, int i);
+// Start of a stage: clears flags (bit i of mask: flags[i]), copies up to two
+// arrays and stamps i, in one launch
+struct CopyJob { double* dst; const double* src; int64_t n; };
+void launch_begin(ba_ctx* c, unsigned mask, CopyJob a, CopyJob b, int i);
+// The end of an LM step, decided on the device so that the host waits once: the
+// update is applied if the step is accepted; block 0 reports to pinned memory.
+// host_ps: the solve's status, or -1: as the solve left it in state.
+struct StepEnd {
+    const double *scal, *pscal;
+    const int *flags, *state, *tri;
+    double* h_scal;      // [0..3] scal, [8..9] pscal
+    int* h_flags;        // [0..2] flags, [3] tri, [4..8] state, [9] accepted
+    u64* stamp;
+    int host_ps;
+};
+__device__ __forceinline__ bool step_end(const StepEnd& E) {
+    const double F = E.scal[0], Fn = E.scal[1], L = E.scal[3] - 0.5 * E.scal[2];
+    const int ps = E.host_ps >= 0 ? E.host_ps : E.state[2];
+    const bool solved = E.host_ps >= 0 || !E.state[4];
+    const bool ok = !E.flags[0] && !E.flags[1] && !E.flags[2] && solved && (ps == BA_OK || ps == BA_ERR_NOT_CONVERGED) &&
+                    L > 0.0 && isfinite(Fn) && Fn < F;
+    if (blockIdx.x == 0) {
+        const int t = threadIdx.x;
+        if (t < 4) E.h_scal[t] = E.scal[t];
+        else if (t < 6) E.h_scal[4 + t] = E.pscal[t - 4];
+        else if (t < 9) E.h_flags[t - 6] = E.flags[t - 6];
+        else if (t == 9) E.h_flags[3] = E.tri ? *E.tri : 0;
+        else if (t < 15) E.h_flags[t - 6] = E.state[t - 10];
+        else if (t == 15) E.h_flags[9] = ok;
+        else if (t == 16) *E.stamp = (u64)wall_clock64();
+    }
+    return ok;
+}
+void launch_linearize(ba_ctx* c, const double* cams, const double* pts, u64* stamp);      // -> J, e, scal[0] = F
 void launch_point(ba_ctx* c, double lambda);
 // linearize + point stage in one pass (J, e, scal[0] = F, K, point terms)
-void launch_linearize_point(ba_ctx* c, const double* cams, const double* pts, double lambda);
+void launch_linearize_point(ba_ctx* c, const double* cams, const double* pts, double lambda, u64* stamp);
 constexpr int kReduceParts = 1024;   // pieces of the first pass of launch_reduce
 // out[j] = sum of part[j*n .. j*n + n) for j < count (<= 3), fixed order
-void launch_reduce(ba_ctx* c, const double* part, int n, int count, double* out);
-void launch_offdiag(ba_ctx* c);
-void launch_diag(ba_ctx* c, double lambda);
-void launch_back_substitute(ba_ctx* c, const double* dxc, double* dxp);
+void launch_reduce(ba_ctx* c, const double* part, int n, int count, double* out, u64* stamp = nullptr);
+void launch_offdiag(ba_ctx* c, u64* stamp);
+void launch_diag(ba_ctx* c, double lambda, u64* stamp);
+void launch_back_substitute(ba_ctx* c, const double* dxc, double* dxp, u64* stamp = nullptr);
 // J_p of the current linearization into Jp if the fused stage left it out
 void ensure_jp(ba_ctx* c);
 void launch_gather_obs(ba_ctx* c, const int32_t* perm, const int32_t* pt_in, const double* uv_in,
                        unsigned long long* bad);
 // |J dx|^2 and dx^T l into scal[2], scal[3] for a dx_p replaced after
 // back-substitution (which forms them for its own dx_p)
-void launch_model_terms(ba_ctx* c, const double* dxc, const double* dxp);
-void launch_evaluate(ba_ctx* c, const double* cams, const double* pts, const double* dxc, const double* dxp);
-void launch_update(ba_ctx* c, double* cams, double* pts, const double* dxc, const double* dxp);
-// PCG: returns status; fills iters/relres (synchronises).  mode 0: block
+void launch_model_terms(ba_ctx* c, const double* dxc, const double* dxp, u64* stamp);
+void launch_evaluate(ba_ctx* c, const double* cams, const double* pts, const double* dxc, const double* dxp, u64* stamp);
+void launch_update(ba_ctx* c, double* cams, double* pts, const double* dxc, const double* dxp, const StepEnd& E);
+// PCG: returns status; fills iters/relres (synchronises).  With wait = false a
+// solve on the chip may still run on return: iters is -1 then and its outcome
+// in c->pcg.state and scal (state[4]: it has to be done again, with wait).
+// begin: stamped by a solve that needs no set-up before k_pcg_init; end: by the
+// solve's last kernel.  mode 0: block
 // diagonal M^-1 (Mblocks [n_rows][81]); mode 1: M^-1 = G^T G from c->fs.
 // defl: deflate the similarity gauge (prepare_deflation first).
 ba_status run_pcg(ba_ctx* c, int mode, const double* Mblocks, int defl, double tol, int max_iter,
-                  const double* x0, double* out, int* iters, double* relres);
+                  const double* x0, double* out, int* iters, double* relres, bool wait = true, u64* begin = nullptr);
 // the solve in one kernel, S held in registers (see kernels_pcg_chip.hip)
 void plan_chip(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P);
 bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, double tol, int max_iter, double* out);
@@ -649,11 +703,11 @@ void launch_csr_spmv(ba_ctx* c, const double* x, double* y);
 // parameters [n_cams][6] + [n_phys][5] (two records per observation), the
 // diagonal stage (damping, padding, rhs, block-Jacobi factors; the blocks
 // come from the pair stage), back-substitution, evaluation and update
-void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, double lambda);
+void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, double lambda, u64* stamp);
 void launch_node_diag(ba_ctx* c, double lambda);
 void launch_back_substitute_shared(ba_ctx* c, const double* dxc, double* dxp);
-void launch_evaluate_shared(ba_ctx* c, const double* params, const double* pts, const double* dxc, const double* dxp);
-void launch_update_shared(ba_ctx* c, double* params, double* pts, const double* dxc, const double* dxp);
+void launch_evaluate_shared(ba_ctx* c, const double* params, const double* pts, const double* dxc, const double* dxp, u64* stamp);
+void launch_update_shared(ba_ctx* c, double* params, double* pts, const double* dxc, const double* dxp, const StepEnd& E);
 // re-triangulation of every point with cameras cams (+ dxc by RCS row when
 // not null): start pts (+ out when delta), linear start if `linear`, n_gn
 // Gauss-Newton steps; out = X, or X - pts when delta; failures counted

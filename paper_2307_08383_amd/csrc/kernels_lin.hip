@@ -171,7 +171,7 @@ __global__ __launch_bounds__(BS) void k_jp_from_K_long(int q0, const int32_t* __
 // in a fixed order (block (b, j); b = 0 with chunk >= n sums the whole
 // vector)
 __global__ __launch_bounds__(BS) void k_reduce(const double* __restrict__ part, int n, int chunk,
-                                               double* __restrict__ out, int ostride) {
+                                               double* __restrict__ out, int ostride, u64* stamp) {
     __shared__ double sh[BS / kWave];
     const int j = blockIdx.y, b = blockIdx.x;
     const double* p = part + (int64_t)j * n;
@@ -180,11 +180,23 @@ __global__ __launch_bounds__(BS) void k_reduce(const double* __restrict__ part, 
     for (int i = lo + threadIdx.x; i < hi; i += BS) s += p[i];
     s = block_sum<BS>(s, sh);
     if (threadIdx.x == 0) out[(int64_t)j * ostride + b] = s;
+    stamp_now(stamp);
+}
+
+__global__ void k_stamp(u64* p) { stamp_now(p); }
+
+__global__ __launch_bounds__(BS) void k_begin(int* __restrict__ flags, unsigned mask, CopyJob a, CopyJob b, u64* stamp) {
+    stamp_now(stamp);
+    const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
+    if (i < 8 && (mask >> i & 1)) flags[i] = 0;
+    if (i < a.n) a.dst[i] = a.src[i];
+    if (i < b.n) b.dst[i] = b.src[i];
 }
 
 __global__ __launch_bounds__(BS) void k_update(int n_cams, int n_pts, const int32_t* __restrict__ cam_row,
                                                double* __restrict__ cams, double* __restrict__ pts,
-                                               const double* __restrict__ dxc, const double* __restrict__ dxp) {
+                                               const double* __restrict__ dxc, const double* __restrict__ dxp, StepEnd E) {
+    if (!step_end(E)) return;
     const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
     if (i < (int64_t)n_cams * 9) {
         const int c = (int)(i / 9), j = (int)(i % 9);
@@ -204,7 +216,7 @@ void launch_project(const double* cams, const double* pts, const int32_t* obs_ca
     k_project<<<nblk(n_obs), BS, 0, st>>>(n_obs, cams, pts, obs_cam, obs_pt, noise, uv);
 }
 
-void launch_linearize(ba_ctx* c, const double* cams, const double* pts) {
+void launch_linearize(ba_ctx* c, const double* cams, const double* pts, u64* stamp) {
     const int n = (int)c->n_obs, nb = nblk(n);
     if (c->precision == BA_MIXED)
         k_linearize<float><<<nb, BS, 0, c->stream>>>(n, c->obs_cam, c->obs_pt, c->obs_uv, cams, pts,
@@ -212,7 +224,7 @@ void launch_linearize(ba_ctx* c, const double* cams, const double* pts) {
     else
         k_linearize<double><<<nb, BS, 0, c->stream>>>(n, c->obs_cam, c->obs_pt, c->obs_uv, cams, pts,
                                                       (double*)c->R, (double*)c->Jp, c->e, c->part, c->flags);
-    launch_reduce(c, c->part, nb, 1, c->scal + 0);
+    launch_reduce(c, c->part, nb, 1, c->scal + 0, stamp);
     c->jp_valid = true;
 }
 
@@ -220,23 +232,29 @@ void launch_linearize(ba_ctx* c, const double* cams, const double* pts) {
 // order: long vectors in two passes (up to kReduceParts contiguous pieces
 // summed by separate blocks into c->part2, then the pieces in order), so
 // that the sum is not left to a single block
-void launch_reduce(ba_ctx* c, const double* part, int n, int count, double* out) {
+void launch_reduce(ba_ctx* c, const double* part, int n, int count, double* out, u64* stamp) {
     constexpr int kPiece = 2048;
     if (n <= 2 * kPiece) {
-        k_reduce<<<dim3(1, count), BS, 0, c->stream>>>(part, n, n, out, 1);
+        k_reduce<<<dim3(1, count), BS, 0, c->stream>>>(part, n, n, out, 1, stamp);
         return;
     }
     const int pieces = std::min(kReduceParts, (n + kPiece - 1) / kPiece);
     const int chunk = (n + pieces - 1) / pieces;
-    k_reduce<<<dim3(pieces, count), BS, 0, c->stream>>>(part, n, chunk, c->part2, kReduceParts);
-    k_reduce<<<dim3(1, count), BS, 0, c->stream>>>(c->part2, kReduceParts, pieces, out, 1);
+    k_reduce<<<dim3(pieces, count), BS, 0, c->stream>>>(part, n, chunk, c->part2, kReduceParts, nullptr);
+    k_reduce<<<dim3(1, count), BS, 0, c->stream>>>(c->part2, kReduceParts, pieces, out, 1, stamp);
 }
 
-void launch_evaluate(ba_ctx* c, const double* cams, const double* pts, const double* dxc, const double* dxp) {
+void launch_evaluate(ba_ctx* c, const double* cams, const double* pts, const double* dxc, const double* dxp, u64* stamp) {
     const int n = (int)c->n_obs, nb = nblk(n);
     k_evaluate<<<nb, BS, 0, c->stream>>>(n, c->obs_cam, c->obs_pt, c->obs_row, c->obs_uv, cams, pts, dxc, dxp,
                                          c->part);
-    launch_reduce(c, c->part, nb, 1, c->scal + 1);   // scal[1] F'
+    launch_reduce(c, c->part, nb, 1, c->scal + 1, stamp);   // scal[1] F'
+}
+
+void launch_stamp(ba_ctx* c, int i) { k_stamp<<<1, 1, 0, c->stream>>>(c->h_stamp + i); }
+
+void launch_begin(ba_ctx* c, unsigned mask, CopyJob a, CopyJob b, int i) {
+    k_begin<<<nblk(std::max<int64_t>({a.n, b.n, 8})), BS, 0, c->stream>>>(c->flags, mask, a, b, c->h_stamp + i);
 }
 
 void launch_gather_obs(ba_ctx* c, const int32_t* perm, const int32_t* pt_in, const double* uv_in,
@@ -268,9 +286,9 @@ void ensure_jp(ba_ctx* c) {
     c->jp_valid = true;
 }
 
-void launch_update(ba_ctx* c, double* cams, double* pts, const double* dxc, const double* dxp) {
+void launch_update(ba_ctx* c, double* cams, double* pts, const double* dxc, const double* dxp, const StepEnd& E) {
     const int64_t n = std::max<int64_t>((int64_t)c->n_cams * 9, (int64_t)c->n_pts * 3);
-    k_update<<<nblk(n), BS, 0, c->stream>>>(c->n_cams, c->n_pts, c->cam_row, cams, pts, dxc, dxp);
+    k_update<<<std::max(1, nblk(n)), BS, 0, c->stream>>>(c->n_cams, c->n_pts, c->cam_row, cams, pts, dxc, dxp, E);
 }
 
 }  // namespace ba

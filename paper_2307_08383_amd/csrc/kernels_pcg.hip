@@ -529,6 +529,7 @@ struct ChipWords {
     double* vec[6];
     double* slots;
     int64_t n_slot;
+    u64* stamp;
 };
 
 // x = x_s (x0 or 0), r = rhs - q0 (q0 = S x0, or 0); deflated: x += W y,
@@ -544,6 +545,7 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
                                                  const double* __restrict__ pW, int n_part, ChipWords cw) {
     __shared__ double sr[RPB][9];
     __shared__ double sh[NP * WPB];
+    stamp_now(cw.stamp);
     double y[kW];
 #pragma unroll
     for (int v = 0; v < kW; ++v) y[v] = 0.0;
@@ -605,6 +607,13 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
         for (int j = 0; j < NP; ++j) pR[(int64_t)NP * blockIdx.x + j] = t[j];
     for (int64_t j = (int64_t)blockIdx.x * BS + threadIdx.x; j < cw.n_slot; j += (int64_t)gridDim.x * BS) cw.slots[j] = 0.0;
     if (blockIdx.x == 0 && threadIdx.x == 0) { state[0] = 0; state[1] = 0; state[2] = BA_OK; state[3] = 0; state[4] = 0; scal[1] = -1.0; }
+}
+
+__global__ void k_report(const int* __restrict__ state, const double* __restrict__ scal, int* __restrict__ h_state,
+                         double* __restrict__ h_scal, u64* stamp) {
+    stamp_now(stamp);
+    if (threadIdx.x < 5) h_state[threadIdx.x] = state[threadIdx.x];
+    if (threadIdx.x < 2) h_scal[threadIdx.x] = scal[threadIdx.x];
 }
 
 // plain y = S x
@@ -1319,14 +1328,20 @@ void prepare_deflation(ba_ctx* c) {
 }
 
 ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, int max_iter, const double* x0,
-                  double* out, int* iters, double* relres) {
+                  double* out, int* iters, double* relres, bool wait, u64* begin) {
     Pcg& P = c->pcg;
     const int nr = c->n_rows, g = grid_of(nr);
     hipStream_t st = c->stream;
     // FULL layout of a system that fits the chip: one kernel, straight from
     // the upper blocks (2,000 cameras: 7.1 us an iteration against 16.8)
     const bool chip = c->chip.G > 0 && !c->upper;
+    if (begin && !chip) launch_stamp(c, (int)(begin - c->h_stamp));
     if (!chip || x0) ensure_sf(c, false);
+    // state and scalars to the host's words, and the end's stamp, in one launch
+    auto report = [&]() {
+        k_report<<<1, 64, 0, st>>>(P.state, P.scal, c->h_flags + 4, c->h_scal + 8, c->h_stamp + kStBack);
+        BA_HIP_CHECK(hipStreamSynchronize(st));
+    };
     const double* q0 = nullptr;
     if (x0) {
         product_cur(c, x0, P.q, st);
@@ -1335,7 +1350,8 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     if (defl) k_defl_Wr<<<g, BS, 0, st>>>(nr, c->rhs, q0, P.W, P.pW);
     ChipWords cw{};
     if (chip)
-        cw = {{P.u, P.q, P.d, P.r[1], P.tb, mode != 0 ? c->fs.tg : nullptr}, P.pE, chip_slot_words()};
+        cw = {{P.u, P.q, P.d, P.r[1], P.tb, mode != 0 ? c->fs.tg : nullptr}, P.pE, chip_slot_words(), begin};
+
     k_pcg_init<<<g, BS, 0, st>>>(nr, c->rhs, q0, x0, mode == 0 ? M : nullptr, P.x, P.r[0], P.z, P.pR, P.state, P.scal,
                                  defl, P.W, P.SW, P.Einv, P.pW, g, cw);
     if (mode != 0) {
@@ -1343,18 +1359,18 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     }
     if (chip) {
         const bool launched = launch_chip(c, mode, M, defl, g, tol, max_iter, out);
-        if (launched) {
-            BA_HIP_CHECK(hipMemcpyAsync(c->h_flags + 4, P.state, 5 * sizeof(int), hipMemcpyDeviceToHost, st));
-            BA_HIP_CHECK(hipMemcpyAsync(c->h_scal + 8, P.scal, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
-            BA_HIP_CHECK(hipStreamSynchronize(st));
+        if (launched && !wait) {
+            *iters = -1;
+            return BA_OK;
         }
+        if (launched) report();
         if (launched && !c->h_flags[8]) {
             *iters = c->h_flags[7];
             *relres = c->h_scal[9];
             return (ba_status)c->h_flags[6];
         }
         c->chip.G = 0;   // not all workgroups ran at once: this context solves with one kernel per phase
-        return run_pcg(c, mode, M, defl, tol, max_iter, x0, out, iters, relres);
+        return run_pcg(c, mode, M, defl, tol, max_iter, x0, out, iters, relres, wait, nullptr);
     }
     launch_A<true>(c, g, tol, max_iter, defl, st);
     if (max_iter > 0) {
@@ -1386,7 +1402,7 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
             c->pcg_graphs.push_back({M, mode, defl, c->s32, c->upper, c->fs.half, tol, max_iter, exec});
         }
     }
-    hipEvent_t evb[2] = {c->ev[12], c->ev[13]};
+    hipEvent_t evb[2] = {c->ev[0], c->ev[1]};
     int* hflag[2] = {c->h_flags + 8, c->h_flags + 12};
     int slot = 0, pending = 0, launched = 0;
     bool done = max_iter == 0;
@@ -1410,10 +1426,8 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
         if (hflag[s_old][0]) done = true;
         if (launched >= n_batches && pending == 0) break;
     }
-    BA_HIP_CHECK(hipMemcpyAsync(c->h_flags + 4, P.state, 4 * sizeof(int), hipMemcpyDeviceToHost, st));
-    BA_HIP_CHECK(hipMemcpyAsync(c->h_scal + 8, P.scal, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
     BA_HIP_CHECK(hipMemcpyAsync(out, P.x, (size_t)nr * 9 * sizeof(double), hipMemcpyDeviceToDevice, st));
-    BA_HIP_CHECK(hipStreamSynchronize(st));
+    report();
     *iters = c->h_flags[7];
     *relres = c->h_scal[9];
     return (ba_status)c->h_flags[6];

@@ -57,7 +57,6 @@ constexpr int kRep = 4;                // replicas of a sum's words
 constexpr int NP = 9;                  // values of a partial (kernels_pcg.hip)
 constexpr int kW = 7;
 constexpr int kSpin = 1 << 21;         // polls before a wait gives up (over a second)
-typedef unsigned long long u64;
 
 struct ChipArgs {
     int max_iter, n_part, s32;
@@ -70,6 +69,7 @@ struct ChipArgs {
     double* out;
     int* state;
     double* scal;
+    u64* stamp;
     u64 *zlo, *zhi, *rlo, *rhi, *tlo, *thi, *slots;    // exchanged words
     const int32_t *gl_ptr, *gl_col, *gu_ptr, *gu_col;  // factor by rows and its transpose by rows
     const float *Gl, *Gu;
@@ -525,6 +525,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
         return;
     }
     if (own) a.out[o] = x;
+    stamp_now(a.stamp);
 }
 
 template <int NB>
@@ -611,7 +612,7 @@ bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, dou
     a.blk = c->blk; a.M = M;
     a.x = P.x; a.r = P.r[0]; a.z = P.z; a.pR = P.pR;
     a.W = P.W; a.SW = P.SW; a.Einv = P.Einv;
-    a.out = out; a.state = P.state; a.scal = P.scal;
+    a.out = out; a.state = P.state; a.scal = P.scal; a.stamp = c->h_stamp + kStBack;
     // vectors of the other kernels and the deflation's partials, free here
     a.zlo = (u64*)P.u; a.zhi = (u64*)P.q; a.rlo = (u64*)P.d; a.rhi = (u64*)P.r[1];
     a.tlo = (u64*)P.tb; a.thi = (u64*)F.tg; a.slots = (u64*)P.pE;

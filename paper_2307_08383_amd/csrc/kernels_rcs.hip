@@ -351,7 +351,9 @@ constexpr int kDeepSteps = 16;
 template <typename T, int kBuf, bool SUB = false>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(kBuf == 2 ? 3 : 2))) void k_offdiag(
     int n_unit, XcdRanges xr, const int32_t* __restrict__ unit_rng, const int32_t* __restrict__ unit_dst,
-    const int32_t* __restrict__ trip, const T* __restrict__ R, double* __restrict__ blk, double* __restrict__ pblk) {
+    const int32_t* __restrict__ trip, const T* __restrict__ R, double* __restrict__ blk, double* __restrict__ pblk,
+    u64* stamp) {
+    stamp_now(stamp);
     constexpr int kVal = 16 / sizeof(T);                             // values per 16-byte chunk
     constexpr int kCh = kRec / kVal;                                 // chunks per record (12 or 6)
     constexpr int kCpl = 4 * kPairWave;                              // couples per step
@@ -560,7 +562,8 @@ __global__ __launch_bounds__(NW * kWave) void k_diag(int n_rows, const int32_t* 
                                              const int32_t* __restrict__ rowobs, const int32_t* __restrict__ row_ptr,
                                              const T* __restrict__ R, const double* __restrict__ ebar, double lambda, double* __restrict__ blk, double* __restrict__ rhs,
                                              double* __restrict__ Minv, double* __restrict__ Linv,
-                                             int* __restrict__ flags) {
+                                             int* __restrict__ flags, u64* stamp) {
+    stamp_now(stamp);
     __shared__ double sred[NW][64];
     __shared__ double S[81], sL[81], L[81];
     const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
@@ -1039,7 +1042,7 @@ void launch_point(ba_ctx* c, double lambda) {
     c->jp_valid = true;
 }
 
-void launch_linearize_point(ba_ctx* c, const double* cams, const double* pts, double lambda) {
+void launch_linearize_point(ba_ctx* c, const double* cams, const double* pts, double lambda, u64* stamp) {
     const int nb = (c->n_chunk + kLinNW - 1) / kLinNW;
     const int n = (int)c->n_obs;
     if (nb + (int64_t)c->n_long > c->n_part)
@@ -1066,12 +1069,15 @@ void launch_linearize_point(ba_ctx* c, const double* cams, const double* pts, do
                                                                      (double*)c->R, c->e, c->ptL, c->obs_rpos,
                                                                      c->ebar, c->part + nb, c->flags);
     }
-    launch_reduce(c, c->part, nb + c->n_long, 1, c->scal + 0);
+    launch_reduce(c, c->part, nb + c->n_long, 1, c->scal + 0, stamp);
     c->jp_valid = false;   // J_p = K L^T where it is needed
 }
 
-void launch_offdiag(ba_ctx* c) {
-    if (c->n_unit == 0) return;
+void launch_offdiag(ba_ctx* c, u64* stamp) {
+    if (c->n_unit == 0) {
+        if (stamp) launch_stamp(c, (int)(stamp - c->h_stamp));
+        return;
+    }
     XcdRanges xr;
     int most = 0;
     for (int x = 0; x < 9; ++x) xr.wv[x] = c->xcd_wv[x];
@@ -1079,16 +1085,16 @@ void launch_offdiag(ba_ctx* c) {
     const int grid = 8 * most;
     if (c->shared)
         k_offdiag<double, 2, true><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                                  (const double*)c->R, c->blk, c->pblk);
+                                                                  (const double*)c->R, c->blk, c->pblk, stamp);
     else if (c->precision == BA_MIXED)
         k_offdiag<float, 2><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                           (const float*)c->R, c->blk, c->pblk);
+                                                           (const float*)c->R, c->blk, c->pblk, stamp);
     else if (c->unit_steps >= (int64_t)kDeepSteps * c->n_unit)
         k_offdiag<double, 3><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                            (const double*)c->R, c->blk, c->pblk);
+                                                            (const double*)c->R, c->blk, c->pblk, stamp);
     else
         k_offdiag<double, 2><<<grid, kWave, 0, c->stream>>>(c->n_unit, xr, c->unit_rng, c->unit_dst, c->trip,
-                                                            (const double*)c->R, c->blk, c->pblk);
+                                                            (const double*)c->R, c->blk, c->pblk, stamp);
     if (c->n_lseg > 0) {
         const int nl = c->n_lseg_long, ns = c->n_lseg - nl;
         const int64_t n = (int64_t)ns * 81;
@@ -1100,22 +1106,25 @@ void launch_offdiag(ba_ctx* c) {
 }
 
 template <typename T>
-void launch_diag_t(ba_ctx* c, double lambda) {
+void launch_diag_t(ba_ctx* c, double lambda, u64* stamp) {
     const T* R = (const T*)c->R;
     if (c->n_rows < kDiagRows)
         k_diag<T, 4><<<c->n_rows, 4 * kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr, R, c->ebar,
-                                                             lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags);
+                                                             lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags, stamp);
     else
         k_diag<T, 1><<<c->n_rows, kWave, 0, c->stream>>>(c->n_rows, c->rowobs_ptr, c->rowobs, c->row_ptr, R, c->ebar,
-                                                         lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags);
+                                                         lambda, c->blk, c->rhs, c->Minv, c->Linv, c->flags, stamp);
 }
 
-void launch_diag(ba_ctx* c, double lambda) {
-    if (c->n_rows == 0) return;
+void launch_diag(ba_ctx* c, double lambda, u64* stamp) {
+    if (c->n_rows == 0) {
+        if (stamp) launch_stamp(c, (int)(stamp - c->h_stamp));
+        return;
+    }
     if (c->precision == BA_MIXED)
-        launch_diag_t<float>(c, lambda);
+        launch_diag_t<float>(c, lambda, stamp);
     else
-        launch_diag_t<double>(c, lambda);
+        launch_diag_t<double>(c, lambda, stamp);
 }
 
 // back-substitution; the model terms go to scal[2] (|J dx|^2) and scal[3]
@@ -1131,17 +1140,20 @@ void launch_back_substitute_t(ba_ctx* c, const double* dxc, double* dxp, int nb,
                                                            dxc, c->e, dxp, c->part + nb, stride);
 }
 
-void launch_back_substitute(ba_ctx* c, const double* dxc, double* dxp) {
+void launch_back_substitute(ba_ctx* c, const double* dxc, double* dxp, u64* stamp) {
     const int nb = (c->n_chunk + kBackNW - 1) / kBackNW;
     const int stride = nb + c->n_long;
-    if (stride == 0) return;
+    if (stride == 0) {
+        if (stamp) launch_stamp(c, (int)(stamp - c->h_stamp));
+        return;
+    }
     if (2 * (int64_t)stride > c->n_part)
         throw ba_hip_error(hipErrorInvalidValue, "model-term partials exceed their buffer", __FILE__, __LINE__);
     if (c->precision == BA_MIXED)
         launch_back_substitute_t<float>(c, dxc, dxp, nb, stride);
     else
         launch_back_substitute_t<double>(c, dxc, dxp, nb, stride);
-    launch_reduce(c, c->part, stride, 2, c->scal + 2);
+    launch_reduce(c, c->part, stride, 2, c->scal + 2, stamp);
 }
 
 // the model terms for dx_p replaced after back-substitution
@@ -1156,17 +1168,20 @@ void launch_model_terms_t(ba_ctx* c, const double* dxc, const double* dxp, int n
                                                                c->ptL, dxc, dxp, c->e, c->part + nb, stride);
 }
 
-void launch_model_terms(ba_ctx* c, const double* dxc, const double* dxp) {
+void launch_model_terms(ba_ctx* c, const double* dxc, const double* dxp, u64* stamp) {
     const int nb = (c->n_chunk + WPB - 1) / WPB;
     const int stride = nb + c->n_long;
-    if (stride == 0) return;
+    if (stride == 0) {
+        if (stamp) launch_stamp(c, (int)(stamp - c->h_stamp));
+        return;
+    }
     if (2 * (int64_t)stride > c->n_part)
         throw ba_hip_error(hipErrorInvalidValue, "model-term partials exceed their buffer", __FILE__, __LINE__);
     if (c->precision == BA_MIXED)
         launch_model_terms_t<float>(c, dxc, dxp, nb, stride);
     else
         launch_model_terms_t<double>(c, dxc, dxp, nb, stride);
-    launch_reduce(c, c->part, stride, 2, c->scal + 2);
+    launch_reduce(c, c->part, stride, 2, c->scal + 2, stamp);
 }
 
 }  // namespace ba

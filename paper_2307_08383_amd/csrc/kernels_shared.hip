@@ -499,7 +499,8 @@ __global__ __launch_bounds__(BS) void k_evaluate_s(int n, const int32_t* __restr
 __global__ __launch_bounds__(BS) void k_update_s(int n_img, int n_phys, int n_pts, int n_free,
                                                  const int32_t* __restrict__ cam_row, double* __restrict__ params,
                                                  double* __restrict__ pts, const double* __restrict__ dxc,
-                                                 const double* __restrict__ dxp) {
+                                                 const double* __restrict__ dxp, StepEnd E) {
+    if (!step_end(E)) return;
     const int64_t i = (int64_t)blockIdx.x * BS + threadIdx.x;
     const int64_t ne = 6 * (int64_t)n_img, nq = 5 * (int64_t)n_phys;
     if (i < ne) {
@@ -517,9 +518,12 @@ inline int nblk(int64_t n) { return (int)((n + BS - 1) / BS); }
 
 }  // namespace
 
-void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, double lambda) {
+void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, double lambda, u64* stamp) {
     const int nb = (c->n_chunk + WPB - 1) / WPB;
-    if (nb + c->n_long == 0) return;
+    if (nb + c->n_long == 0) {
+        if (stamp) launch_stamp(c, (int)(stamp - c->h_stamp));
+        return;
+    }
     if (nb + (int64_t)c->n_long > c->n_part)
         throw ba_hip_error(hipErrorInvalidValue, "cost partials exceed their buffer", __FILE__, __LINE__);
     if (nb > 0)
@@ -532,7 +536,7 @@ void launch_linpoint_shared(ba_ctx* c, const double* params, const double* pts, 
                                                            c->obs_pt, c->img_cam, c->n_cams, c->obs_uv, params, pts,
                                                            lambda, (double*)c->R, (double*)c->Jp, c->e, c->ptL,
                                                            c->ebar, c->part + nb, c->flags);
-    launch_reduce(c, c->part, nb + c->n_long, 1, c->scal + 0);
+    launch_reduce(c, c->part, nb + c->n_long, 1, c->scal + 0, stamp);
 }
 
 void launch_node_diag(ba_ctx* c, double lambda) {
@@ -560,18 +564,18 @@ void launch_back_substitute_shared(ba_ctx* c, const double* dxc, double* dxp) {
                                                           c->ptL, dxc, dxp);
 }
 
-void launch_evaluate_shared(ba_ctx* c, const double* params, const double* pts, const double* dxc, const double* dxp) {
+void launch_evaluate_shared(ba_ctx* c, const double* params, const double* pts, const double* dxc, const double* dxp, u64* stamp) {
     const int n = (int)c->n_obs, nb = nblk(n);
     k_evaluate_s<<<nb, BS, 0, c->stream>>>(n, c->obs_cam, c->obs_pt, c->obs_row, c->img_cam, c->n_cams, c->n_free,
                                            c->obs_uv, params, pts, dxc, dxp, (const double*)c->R, (const double*)c->Jp,
                                            c->e, c->part, nb);
-    launch_reduce(c, c->part, nb, 3, c->scal + 1);
+    launch_reduce(c, c->part, nb, 3, c->scal + 1, stamp);
 }
 
-void launch_update_shared(ba_ctx* c, double* params, double* pts, const double* dxc, const double* dxp) {
+void launch_update_shared(ba_ctx* c, double* params, double* pts, const double* dxc, const double* dxp, const StepEnd& E) {
     const int64_t n = std::max<int64_t>(6 * (int64_t)c->n_cams + 5 * (int64_t)c->n_phys, 3 * (int64_t)c->n_pts);
-    k_update_s<<<nblk(n), BS, 0, c->stream>>>(c->n_cams, c->n_phys, c->n_pts, c->n_free, c->cam_row, params, pts,
-                                              dxc, dxp);
+    k_update_s<<<std::max(1, nblk(n)), BS, 0, c->stream>>>(c->n_cams, c->n_phys, c->n_pts, c->n_free, c->cam_row,
+                                                           params, pts, dxc, dxp, E);
 }
 
 }  // namespace ba
