@@ -55,110 +55,142 @@ __global__ __launch_bounds__(BS) void k_fsai_norm(int64_t n_blk, const int32_t* 
     }
 }
 
-// Cholesky of a 9x9 SPD tile by the 64 lanes of one wave (lane l < 45 holds
-// lower element (r, c), l = r(r+1)/2 + c); writes L (lower, zero upper) over
-// T; returns false if a pivot was not positive (the wave's lanes agree).
-__device__ __forceinline__ bool chol9_wave(float* T) {
-    const int l = threadIdx.x % kWave;
-    const bool act = l < 45;
-    int rr = 0;
-    while (act && (rr + 1) * (rr + 2) / 2 <= l) ++rr;
-    const int cc = act ? l - rr * (rr + 1) / 2 : 0;
-    float v = act ? T[rr * 9 + cc] : 0.f;
+__device__ __forceinline__ float lane_value(float v, int l) {   // l: the same for all lanes
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
+__device__ __forceinline__ float quotient(float v, float root, float inv) {   // v / root, the product corrected once
+    const float w = v * inv;
+    return fmaf(fmaf(-w, root, v), inv, w);
+}
+
+// Cholesky of a 9x9 SPD tile by one wave: lane r < 9 holds row r, a pivot's
+// column reaches the other lanes as scalars.  a: row r of L (above the
+// diagonal: undefined); root, inv: L's diagonal and its reciprocals.  Returns
+// false if a pivot was not positive.
+__device__ __forceinline__ bool chol9(const float* T, int lane, float* a, float* root, float* inv) {
+    const int r = min(lane, 8);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) a[q] = T[r * 9 + q];
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const float dkk = __shfl(v, k * (k + 1) / 2 + k, kWave);
-        ok = ok && dkk > 0.f;
-        const float s = dkk > 0.f ? sqrtf(dkk) : 1.f;
-        if (act && cc == k) v = (rr == k) ? s : v / s;
-        const bool upd = act && cc > k;
-        const int la = upd ? rr * (rr + 1) / 2 + k : 0;
-        const int lc = upd ? cc * (cc + 1) / 2 + k : 0;
-        const float x = __shfl(v, la, kWave);
-        const float y = __shfl(v, lc, kWave);
-        if (upd) v -= x * y;
-    }
-    if (act) {
-        T[rr * 9 + cc] = v;
-        if (rr != cc) T[cc * 9 + rr] = 0.f;
+        const float d = lane_value(a[k], k);
+        ok = ok && d > 0.f;
+        // 1 / sqrt(d) and sqrt(d), each corrected once
+        const float d1 = d > 0.f ? d : 1.f;
+        float y = __builtin_amdgcn_rsqf(d1), s = d1 * y;
+        s = fmaf(0.5f * y, fmaf(-s, s, d1), s);
+        y = fmaf(y, fmaf(-s, y, 1.f), y);
+        root[k] = s;
+        inv[k] = y;
+        const float l = quotient(a[k], s, y);   // L[r][k] in the lanes r >= k
+        a[k] = l;
+#pragma unroll
+        for (int c = k + 1; c < 9; ++c) a[c] -= l * lane_value(l, c);
     }
     return ok;
 }
 
-// One workgroup per RCS row.
-__global__ __launch_bounds__(BS) void k_fsai(const int32_t* __restrict__ fs_ptr, const int32_t* __restrict__ fs_J,
+// One workgroup per RCS row: up to 28 tiles a side, 406 of 324 bytes in LDS, so
+// one workgroup a CU, and the time is a row's chain of m steps (a 2,000-camera
+// grid's rows hold about 20 tiles a side).  So a step is kept short:
+//   - the waves that have panel rows factor the diagonal tile each for itself,
+//     in registers: no barrier between the two, and no division in the panel;
+//   - the trailing matrix stays in registers, three rows of a tile per thread
+//     (tasks in order of their column, so that whole waves fall idle as the
+//     columns are done); a column goes to LDS when its turn comes;
+//   - the last block row of the inverse is found from right to left with the
+//     sums kept in registers and the stored inverses of the diagonal factors.
+// Two barriers a step each way.  Measured against 256 threads with the trailing
+// matrix in LDS, the factor by one wave through shuffles and divisions in the
+// panel: 300 rows of 28 tiles a side 525 -> 226 us, 2,000 rows 1,387 -> 618.
+// (Panel rows as products with the factor's inverse: 230 and 625 us, but an
+// error against FP64 1.1 to 3 times as large; this form's is that of before:
+// 6.8e-8, 6.2e-8, 7.3e-8 and 1.0e-7 of G's norm on four blocks, 6.8e-8, 6.9e-8,
+// 7.2e-8 and 1.0e-7 before.)
+constexpr int FT = 1024;
+constexpr int kOwn = (kFsaiTiles * 3 + FT - 1) / FT;            // tile thirds of a thread
+constexpr int kOwnR = ((kFsaiM - 1) * 81 + FT - 1) / FT;        // sums of the last row of a thread
+
+__global__ __launch_bounds__(FT) void k_fsai(const int32_t* __restrict__ fs_ptr, const int32_t* __restrict__ fs_J,
                                              const int32_t* __restrict__ fs_slot, const int64_t* __restrict__ fs_tptr,
                                              const int32_t* __restrict__ fs_tile, const float* __restrict__ An,
                                              const double* __restrict__ Linv, const int32_t* __restrict__ gu_pos,
                                              float* __restrict__ G, float* __restrict__ Gl, float* __restrict__ Gu,
                                              int* __restrict__ flags) {
-    __shared__ float T[kFsaiTiles][81];
-    __shared__ float sP[3][81];
-    __shared__ float sC[81];
+    extern __shared__ float sT[];   // tiles (a, b), a >= b
+    __shared__ float sP[81];
     __shared__ int s_bad;
     const int row = blockIdx.x;
     const int j0 = fs_ptr[row], m = fs_ptr[row + 1] - j0;
     const int32_t* tiles = fs_tile + fs_tptr[row];
-    const int nt = m * (m + 1) / 2;
+    const int nt = m * (m + 1) / 2, last = m - 1;
+    const int tid = threadIdx.x, lane = tid % kWave;
+    auto tile = [&](int a, int b) { return sT + tix(a, b) * 81; };
     // tiles (a, b), a >= b: Ahat(J_a, J_b) = An[(J_b, J_a)]^T
-    for (int e = threadIdx.x; e < nt * 81; e += BS) {
-        const int ti = e / 81, pq = e % 81;
-        const int kb = tiles[ti];
-        float v;
-        if (kb == -2)
-            v = (pq / 9 == pq % 9) ? 1.f : 0.f;
-        else if (kb < 0)
-            v = 0.f;
-        else
-            v = An[(int64_t)kb * 81 + (pq % 9) * 9 + pq / 9];
-        T[ti][pq] = v;
+    float acc[kOwn][27];
+    int ta[kOwn], tc[kOwn], tp[kOwn];   // tile (ta, tc), rows tp .. tp + 2; tc = -1: none
+#pragma unroll
+    for (int s = 0; s < kOwn; ++s) {
+        const int task = tid + s * FT;
+        ta[s] = 0; tc[s] = -1; tp[s] = task % 3 * 3;
+        if (task >= nt * 3) continue;
+        const int rev = nt - 1 - task / 3;   // column by column, from the last one backwards
+        int w = (int)((sqrtf(8.f * (float)rev + 1.f) - 1.f) * 0.5f);
+        if ((w + 1) * (w + 2) / 2 <= rev) ++w;
+        if (w * (w + 1) / 2 > rev) --w;
+        tc[s] = last - w;
+        ta[s] = last - (rev - w * (w + 1) / 2);
+        const int kb = tiles[tix(ta[s], tc[s])];
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const int p = tp[s] + r;
+                acc[s][r * 9 + q] = kb == -2 ? (p == q ? 1.f : 0.f) : kb < 0 ? 0.f : An[(int64_t)kb * 81 + q * 9 + p];
+            }
+        if (tc[s] == 0)
+#pragma unroll
+            for (int v = 0; v < 27; ++v) tile(ta[s], 0)[tp[s] * 9 + v] = acc[s][v];
     }
-    if (threadIdx.x == 0) s_bad = 0;
-    __syncthreads();
+    if (tid == 0) s_bad = 0;
     for (int b = 0; b < m; ++b) {
-        if (threadIdx.x < kWave) {
-            const bool ok = chol9_wave(T[tix(b, b)]);
-            if (!ok && threadIdx.x == 0) s_bad = 1;
-        }
-        __syncthreads();
-        // panel: L_ab L_bb^T = T_ab, row p of L_ab by forward substitution
-        // (one thread per (a, p))
-        const float* Lbb = T[tix(b, b)];
-        const int np = (m - 1 - b) * 9;
-        for (int task = threadIdx.x; task < np; task += BS) {
-            const int a = b + 1 + task / 9, p = task % 9;
-            float* Tr = &T[tix(a, b)][p * 9];
-            float x[9];
+        __syncthreads();   // column b is in LDS
+        const int np = (last - b) * 9;   // panel rows
+        float l[9];
+        if (tid - lane < max(np, 1)) {
+            float root[9], inv[9];
+            const bool ok = chol9(tile(b, b), lane, l, root, inv);
+            if (!ok && tid == 0) s_bad = 1;
+            // L_ab L_bb^T = T_ab, row p by forward substitution
+            float* Tr = tid < np ? tile(b + 1 + tid / 9, b) + tid % 9 * 9 : sP;
+            float t[9];
+#pragma unroll
+            for (int u = 0; u < 9; ++u) t[u] = tid < np ? Tr[u] : 0.f;
 #pragma unroll
             for (int q = 0; q < 9; ++q) {
-                float s = Tr[q];
+                t[q] = quotient(t[q], root[q], inv[q]);
 #pragma unroll
-                for (int c = 0; c < q; ++c) s -= x[c] * Lbb[q * 9 + c];
-                x[q] = s / Lbb[q * 9 + q];
+                for (int u = q + 1; u < 9; ++u) t[u] -= t[q] * lane_value(l[q], u);
             }
+            if (tid < np)
 #pragma unroll
-            for (int q = 0; q < 9; ++q) Tr[q] = x[q];
+                for (int q = 0; q < 9; ++q) Tr[q] = t[q];
         }
         __syncthreads();
-        // trailing update: T_ac -= L_ab L_cb^T for b < c <= a, one thread
-        // per (tile, three rows)
-        const int nrem = m - 1 - b;
-        const int ntask = nrem * (nrem + 1) / 2 * 3;
-        for (int task = threadIdx.x; task < ntask; task += BS) {
-            const int tt = task / 3, p0 = (task % 3) * 3;
-            int a2 = 0;
-            while ((a2 + 1) * (a2 + 2) / 2 <= tt) ++a2;
-            const int c2 = tt - a2 * (a2 + 1) / 2;
-            const int a = b + 1 + a2, c = b + 1 + c2;
-            const float* La = T[tix(a, b)];
-            const float* Lc = T[tix(c, b)];
-            float* Out = T[tix(a, c)];
-            float lr[3][9];
+        if (tid < 9)
 #pragma unroll
-            for (int r = 0; r < 3; ++r)
+            for (int q = 0; q < 9; ++q) tile(b, b)[tid * 9 + q] = l[q];
+        // trailing update: T_ac -= L_ab L_cb^T for b < c <= a
 #pragma unroll
-                for (int u = 0; u < 9; ++u) lr[r][u] = La[(p0 + r) * 9 + u];
+        for (int s = 0; s < kOwn; ++s) {
+            if (tc[s] <= b) continue;
+            const float* La = tile(ta[s], b) + tp[s] * 9;
+            const float* Lc = tile(tc[s], b);
+            float lr[27];
+#pragma unroll
+            for (int v = 0; v < 27; ++v) lr[v] = La[v];
 #pragma unroll
             for (int q = 0; q < 9; ++q) {
                 float lc[9];
@@ -166,79 +198,78 @@ __global__ __launch_bounds__(BS) void k_fsai(const int32_t* __restrict__ fs_ptr,
                 for (int u = 0; u < 9; ++u) lc[u] = Lc[q * 9 + u];
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
-                    float s = 0.f;
+                    float v = 0.f;
 #pragma unroll
-                    for (int u = 0; u < 9; ++u) s += lr[r][u] * lc[u];
-                    Out[(p0 + r) * 9 + q] -= s;
+                    for (int u = 0; u < 9; ++u) v += lr[r * 9 + u] * lc[u];
+                    acc[s][r * 9 + q] -= v;
                 }
             }
+            if (tc[s] == b + 1)
+#pragma unroll
+                for (int v = 0; v < 27; ++v) tile(ta[s], b + 1)[tp[s] * 9 + v] = acc[s][v];
         }
-        __syncthreads();
     }
-    // last block row of L^-1: R_{m-1} = L_{m-1,m-1}^-1; for b < m-1
-    // R_b L_bb = -(sum_{a > b} R_a L_ab).  R_a is kept in tile (m-1, a)
-    // (tile (m-1, b) still holds L_{m-1,b} when R_b is formed).
-    const int last = m - 1;
-    if (threadIdx.x < 9) {
-        // column c of L^-1 by forward substitution
-        const int c = threadIdx.x;
-        const float* L = T[tix(last, last)];
+    __syncthreads();
+    // the inverses of the diagonal factors, all at once: a column per thread
+    {
+        const int c = tid % 9, b = tid / 9;
         float x[9];
+        if (b < m) {
+            const float* L = tile(b, b);
 #pragma unroll
-        for (int r = 0; r < 9; ++r) {
-            float s = (r == c) ? 1.f : 0.f;
+            for (int r = 0; r < 9; ++r) {
+                float v = r == c ? 1.f : 0.f;
 #pragma unroll
-            for (int q = 0; q < r; ++q) s -= L[r * 9 + q] * x[q];
-            x[r] = r < c ? 0.f : s / L[r * 9 + r];
+                for (int q = 0; q < r; ++q) v -= L[r * 9 + q] * x[q];
+                x[r] = r < c ? 0.f : v / L[r * 9 + r];
+            }
         }
+        __syncthreads();
+        if (b < m)
 #pragma unroll
-        for (int r = 0; r < 9; ++r) sC[r * 9 + c] = x[r];
+            for (int r = 0; r < 9; ++r) tile(b, b)[r * 9 + c] = x[r];
+        __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x < 81) T[tix(last, last)][threadIdx.x] = sC[threadIdx.x];
-    __syncthreads();
-    for (int b = last - 1; b >= 0; --b) {
-        if (threadIdx.x < 243) {
-            const int part = threadIdx.x / 81, pq = threadIdx.x % 81, p = pq / 9, q = pq % 9;
-            float s = 0.f;
-            for (int a = b + 1 + part; a <= last; a += 3) {
-                const float* Ra = T[tix(last, a)];
-                const float* Lab = T[tix(a, b)];
+    // last block row of L^-1: R_last = L_last,last^-1; for b < last
+    // R_b = -(sum_{a > b} R_a L_ab) L_bb^-1.  R_b is kept in tile (last, b),
+    // whose L_last,b every sum takes in the first step.
+    float sum[kOwnR];
 #pragma unroll
-                for (int u = 0; u < 9; ++u) s += Ra[p * 9 + u] * Lab[u * 9 + q];
-            }
-            sP[part][pq] = s;
+    for (int s = 0; s < kOwnR; ++s) sum[s] = 0.f;
+    for (int a = last; a > 0; --a) {
+        const float* Ra = tile(last, a);
+#pragma unroll
+        for (int s = 0; s < kOwnR; ++s) {
+            const int e = tid + s * FT, b = e / 81, pq = e % 81, p = pq / 9, q = pq % 9;
+            if (b >= a) continue;
+            const float* Lab = tile(a, b);
+            float v = 0.f;
+#pragma unroll
+            for (int u = 0; u < 9; ++u) v += Ra[p * 9 + u] * Lab[u * 9 + q];
+            sum[s] += v;
+            if (b == a - 1) sP[pq] = -sum[s];
         }
         __syncthreads();
-        if (threadIdx.x < 9) {
-            // row p of R_b: R_b L_bb = -C, backward over q
-            const int p = threadIdx.x;
-            const float* Lbb = T[tix(b, b)];
-            float r[9];
+        if (tid < 81) {
+            const int p = tid / 9, q = tid % 9;
+            const float* Li = tile(a - 1, a - 1);
+            double v = 0.0;
 #pragma unroll
-            for (int q = 8; q >= 0; --q) {
-                float s = -(sP[0][p * 9 + q] + sP[1][p * 9 + q] + sP[2][p * 9 + q]);
-#pragma unroll
-                for (int u = q + 1; u < 9; ++u) s -= r[u] * Lbb[u * 9 + q];
-                r[q] = s / Lbb[q * 9 + q];
-            }
-#pragma unroll
-            for (int q = 0; q < 9; ++q) sC[p * 9 + q] = r[q];
+            for (int u = 0; u < 9; ++u) v += (double)sP[p * 9 + u] * (double)Li[u * 9 + q];
+            tile(last, a - 1)[tid] = (float)v;
         }
-        __syncthreads();
-        if (threadIdx.x < 81) T[tix(last, b)][threadIdx.x] = sC[threadIdx.x];
         __syncthreads();
     }
     // G_{i, J_b} = R_b L_{J_b}^-1 (FP64 accumulation); block-Jacobi row if
     // the local factorisation failed
     const bool bad = s_bad != 0;
-    for (int e = threadIdx.x; e < m * 81; e += BS) {
+    for (int e = tid; e < m * 81; e += FT) {
         const int b = e / 81, pq = e % 81, p = pq / 9, q = pq % 9;
         const int j = fs_J[j0 + b];
         const double* Lj = Linv + (int64_t)j * 81;
         double s = 0.0;
         if (!bad) {
-            const float* Rb = T[tix(last, b)];
+            const float* Rb = tile(last, b);
             for (int u = q; u < 9; ++u) s += (double)Rb[p * 9 + u] * Lj[u * 9 + q];
         } else if (b == last) {
             s = Lj[pq];
@@ -248,7 +279,7 @@ __global__ __launch_bounds__(BS) void k_fsai(const int32_t* __restrict__ fs_ptr,
         Gl[(int64_t)(j0 + b) * 81 + pq] = g;
         Gu[(int64_t)gu_pos[j0 + b] * 81 + q * 9 + p] = g;
     }
-    if (bad && threadIdx.x == 0) atomicAdd(flags + 2, 1);
+    if (bad && tid == 0) atomicAdd(flags + 2, 1);
 }
 
 }  // namespace
@@ -258,8 +289,9 @@ void launch_fsai(ba_ctx* c) {
     if (nb > 0)
         k_fsai_norm<<<(unsigned)((nb + 2) / 3), BS, 0, c->stream>>>(nb, c->fs.brow, c->col_idx, c->blk, c->Linv,
                                                                     c->fs.An);
+    const size_t lds = (size_t)c->fs.max_m * (c->fs.max_m + 1) / 2 * 81 * sizeof(float);
     if (c->n_rows > 0)
-        k_fsai<<<c->n_rows, BS, 0, c->stream>>>(c->fs.ptr, c->fs.J, c->fs.slot, c->fs.tptr, c->fs.tile, c->fs.An,
+        k_fsai<<<c->n_rows, FT, lds, c->stream>>>(c->fs.ptr, c->fs.J, c->fs.slot, c->fs.tptr, c->fs.tile, c->fs.An,
                                                 c->Linv, c->upper ? c->fs.gl_self : c->fs.gu_pos, c->fs.G, c->fs.Gl,
                                                 c->fs.Gu, c->flags);
     c->fs.gu_upper = c->upper;
