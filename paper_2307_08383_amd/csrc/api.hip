@@ -61,7 +61,7 @@ void upload(ba_ctx* c, T** p, const std::vector<T>& h) {
 void free_ctx(ba_ctx* c) {
     if (!c) return;
     void* ptrs[] = {c->obs_cam, c->obs_pt, c->obs_row, c->obs_uv, c->chunk_q, c->chunk_ptr, c->long_ptr, c->cam_row,
-                    c->row_ptr, c->col_idx, c->trip, c->chip.brow, c->chip.cptr, c->chip.cols, c->rowobs_ptr, c->rowobs,
+                    c->row_ptr, c->col_idx, c->trip, c->chip.brow, c->chip.cptr, c->chip.cols, c->chip_ord.cptr, c->chip_ord.cols, c->rowobs_ptr, c->rowobs,
                     c->sf_ptr, c->sf_col, c->sf_src, c->Sf, c->Sf32, c->Su32, c->lo_ptr, c->lo_blk, c->unit_rng, c->unit_dst, c->lseg_blk, c->lseg_ptr, c->pblk, c->R, c->Jp, c->e, c->obs_rpos, c->ebar, c->ptL, c->blk, c->rhs, c->Minv,
                     c->Linv, c->Mlearn, c->dxc, c->dxp, c->part, c->part2, c->scal, c->flags, c->pcg.x, c->pcg.r[0],
                     c->pcg.r[1], c->pcg.z, c->pcg.q, c->pcg.d, c->pcg.t, c->pcg.u, c->pcg.tb, c->pcg.pA, c->pcg.pR, c->pcg.W, c->pcg.SW, c->pcg.Einv,
@@ -625,11 +625,12 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         }
         c->n_slice = (int32_t)slice_cam.size();
     }
-    ba::ChipPlan cp;
+    ba::ChipPlan cp, co;
     {
         int n_cu = 0;
         BA_HIP_CHECK(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
         ba::plan_chip(nr, sf_ptr.data(), sf_col.data(), n_cu, cp);
+        ba::plan_chip_ordered(nr, sf_ptr.data(), sf_col.data(), n_cu, co);
     }
     ph.mark("chip plan");
     std::vector<int32_t> row_ptr32(row_ptr.begin(), row_ptr.end());
@@ -661,6 +662,12 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         upload(c, &c->chip.cols, cp.cols);
         c->chip.G = cp.G;
         c->chip.NB = cp.NB;
+    }
+    if (co.G > 0) {
+        upload(c, &c->chip_ord.cptr, co.cptr);
+        upload(c, &c->chip_ord.cols, co.cols);
+        c->chip_ord.G = co.G;
+        c->chip_ord.NB = co.NB;
     }
     if (shared) {
         upload(c, &c->img_cam, c->h_img_cam);
@@ -1520,7 +1527,7 @@ ba_status ba_lm_step(ba_ctx* c, double* cams, double* pts, ba_lm_state* st, cons
         if (it < 0 && c->h_flags[8]) {
             // not all workgroups of the solve ran at once, nothing was updated:
             // this context solves with one kernel per phase from now on
-            c->chip.G = 0;
+            c->chip.G = c->chip_ord.G = 0;
             solve(true);
             finish();
         } else if (it < 0) {

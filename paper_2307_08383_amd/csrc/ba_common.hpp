@@ -53,11 +53,10 @@ __device__ __forceinline__ void rot_coeffs(double s, double& a, double& b, doubl
         bs = -1.0 / 24 + s * (2.0 / 720 + s * (-3.0 / 40320 + s * (4.0 / 3628800 + s * (-5.0 / 479001600 + s * (6.0 / 87178291200.0 + s * (-7.0 / 20922789888000.0))))));
     } else {
         const double th = sqrt(s), it = 1.0 / th, is = it * it;   // one division
-        double sh, ch;
-        sincos(0.5 * th, &sh, &ch);   // the half angle gives all three
-        const double sn = 2.0 * sh * ch;
+        double sn, cs;
+        sincos(th, &sn, &cs);
+        const double sh = sin(0.5 * th);
         const double omc = 2.0 * sh * sh;   // 1 - cos th without cancellation
-        const double cs = 1.0 - omc;
         a = sn * it;
         b = omc * is;
         as = (th * cs - sn) * (0.5 * is * it);
@@ -249,11 +248,12 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Sums over the wave of 64 values a lane: lane l receives the total of value
-// l.  Each step halves the values a lane holds (one half stays, the other goes
-// to a partner lane), 63 exchanges in all instead of six a value: lane ^ 32
-// and lane ^ 16 by register swaps, then the mirrored lane within 16 and within
-// 8 and lanes ^ 2, ^ 1 (DPP).  The diagonal stage of 16 rows 16.3 -> 8.6 us, of
+// Sums over the wave of 64 values a lane, each bit for bit that of wave_sum:
+// value wave_sums64_at(l) ends in lane l.  Each step halves the values a lane
+// holds (one half stays, the other goes to a partner lane), 63 exchanges in all
+// instead of six a value, in wave_sum's order of partners.  A mirrored lane
+// differs in all the bits below, so the halves go by sums of two bits, which
+// the later partners share.  The diagonal stage of 16 rows 16.3 -> 8.6 us, of
 // 2,000 rows 95 -> 90, against wave_sum of each value.
 template <int CTRL, int H>
 __device__ __forceinline__ void halve_dpp(double* v, bool up) {
@@ -275,14 +275,18 @@ __device__ __forceinline__ void halve_swap(double* v, Swap&& swap) {
                __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
     }
 }
+__device__ __forceinline__ int wave_sums64_at(int l) {
+    const int b0 = l & 1, b1 = l >> 1 & 1, b2 = l >> 2 & 1, b3 = l >> 3 & 1, b4 = l >> 4 & 1, b5 = l >> 5 & 1;
+    return (b0 ^ b2) << 5 | (b1 ^ b2) << 4 | (b2 ^ b3) << 3 | b3 << 2 | b4 << 1 | b5;
+}
 __device__ __forceinline__ double wave_sums64(double (&v)[64]) {
-    const int lane = threadIdx.x % kWave;
-    halve_swap<32>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); });
-    halve_swap<16>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); });
-    halve_dpp<0x140, 8>(v, lane & 8);
-    halve_dpp<0x141, 4>(v, lane & 4);
-    halve_dpp<0x4E, 2>(v, lane & 2);
-    halve_dpp<0xB1, 1>(v, lane & 1);
+    const int at = wave_sums64_at(threadIdx.x % kWave);
+    halve_dpp<0xB1, 32>(v, at & 32);    // lane ^ 1
+    halve_dpp<0x4E, 16>(v, at & 16);    // lane ^ 2
+    halve_dpp<0x141, 8>(v, at & 8);     // mirrored within 8
+    halve_dpp<0x140, 4>(v, at & 4);     // mirrored within 16
+    halve_swap<2>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); });
+    halve_swap<1>(v, [](unsigned a, unsigned b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); });
     return v[0];
 }
 
@@ -562,7 +566,7 @@ struct ba_ctx {
     ba::Pcg pcg;
     ba::Fsai fs;
     ba::Csr csr;
-    ba::Chip chip;
+    ba::Chip chip, chip_ord;
     hipEvent_t ev[2] = {};             // the two batches of iterations in flight
     // Time stamps of the stages (100 MHz clock), written to pinned memory by
     // the stages' own kernels: an event in the stream between two kernels held
@@ -682,6 +686,8 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* Mblocks, int defl, double t
                   const double* x0, double* out, int* iters, double* relres, bool wait = true, u64* begin = nullptr);
 // the solve in one kernel, S held in registers (see kernels_pcg_chip.hip)
 void plan_chip(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P);
+void plan_chip_ordered(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P);
+bool launch_chip_ordered(ba_ctx* c, const double* M, int n_part, double tol, int max_iter, double* out);
 bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, double tol, int max_iter, double* out);
 int64_t chip_slot_words();
 // gauge vectors of the last linearization's cameras, S W and (W^T S W)^-1

@@ -1333,8 +1333,18 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     const int nr = c->n_rows, g = grid_of(nr);
     hipStream_t st = c->stream;
     // FULL layout of a system that fits the chip: one kernel, straight from
-    // the upper blocks (2,000 cameras: 7.1 us an iteration against 16.8)
-    const bool chip = c->chip.G > 0 && !c->upper;
+    // the upper blocks (2,000 cameras: 6.6 us an iteration against 16.8).  The
+    // result of a solve to a loose tolerance hangs on the order of its sums:
+    // after 100 iterations the residual is another one by 0.1 to 4% for any
+    // other order (2,000 cameras, block-Jacobi), so that the stop test of 1e-6
+    // ends one or two iterations earlier or later in 5 of 12 scenes, with
+    // parameters 1e-7 apart.  Such a solve keeps the order of the kernels below,
+    // in one kernel too where that has a form (7.8 us) and with these kernels
+    // otherwise.  Below kChipTol the iterates agree whatever the order (at
+    // 1e-10 to 1e-11, at 1e-12 to 1e-12).
+    constexpr double kChipTol = 1e-8;
+    const bool ordered = tol > kChipTol && !c->upper && mode == 0 && !defl && c->chip_ord.G > 0;
+    const bool chip = ordered || (c->chip.G > 0 && !c->upper && tol <= kChipTol);
     if (begin && !chip) launch_stamp(c, (int)(begin - c->h_stamp));
     if (!chip || x0) ensure_sf(c, false);
     // state and scalars to the host's words, and the end's stamp, in one launch
@@ -1358,7 +1368,8 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
         launch_factor_init(c, g, defl, st);
     }
     if (chip) {
-        const bool launched = launch_chip(c, mode, M, defl, g, tol, max_iter, out);
+        const bool launched = ordered ? launch_chip_ordered(c, M, g, tol, max_iter, out)
+                                      : launch_chip(c, mode, M, defl, g, tol, max_iter, out);
         if (launched && !wait) {
             *iters = -1;
             return BA_OK;
@@ -1369,7 +1380,7 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
             *relres = c->h_scal[9];
             return (ba_status)c->h_flags[6];
         }
-        c->chip.G = 0;   // not all workgroups ran at once: this context solves with one kernel per phase
+        c->chip.G = c->chip_ord.G = 0;   // not all workgroups ran at once: this context solves with one kernel per phase
         return run_pcg(c, mode, M, defl, tol, max_iter, x0, out, iters, relres, wait, nullptr);
     }
     launch_A<true>(c, g, tol, max_iter, defl, st);

@@ -10,15 +10,17 @@
 // vector z (with the factorised preconditioner also r' and t) with the
 // workgroups that own neighbouring rows.  The second sum (r^T z, r^T r, the
 // deflation's (S W)^T z) is taken after the next product, so it costs no
-// wait.  On the 2,000-camera block (198 workgroups) an iteration takes 7.1 us:
-// 2.3 for the first sum, 1.9 for the exchange, 1.2 for the product with its
-// row sums, 0.6 to collect the second sum, the rest barriers and the row's
-// own work.  One kernel per phase instead (each followed by the partial sums
-// and the index, block and vector loads that depend on each other) took
-// 16.8 us.  Per iteration against those kernels: 16 cameras in one workgroup
-// 2.7 us (7.9), 84 rows of shared intrinsics 5.3 (10.8), 300 cameras with a
-// dense S and FSAI 23 (37.8), FSAI with deflation on the 2,000-camera block
-// 21.7 (26.4: its factors stay in the L2s and it exchanges three vectors).
+// wait; its words are asked for before the product, and z goes out before the
+// sums are formed, so that the first poll for it finds it.  On the 2,000-camera
+// block (198 workgroups) an iteration takes 6.6 us, on 300 cameras (36) 4.7:
+// 2.5 (1.2) for the first sum, 1.5 for the exchange, 1.2 for the product with
+// its row sums, the rest barriers and the row's own work.  One kernel per phase
+// instead (each followed by the partial sums and the index, block and vector
+// loads that depend on each other) took 16.8 us.  Per iteration against those
+// kernels: 16 cameras in one workgroup 2.7 us (7.9), 84 rows of shared
+// intrinsics 4.5 (10.8), 300 cameras with a dense S and FSAI 22 (37.8), FSAI
+// with deflation on the 2,000-camera block 21.7 (26.4: its factors stay in the
+// L2s and it exchanges three vectors).
 //
 // Exchange: a double travels as two 8-byte words, each half the value and
 // the number of the exchange it belongs to.  Words are written and read with
@@ -123,6 +125,7 @@ template <int NB, bool FACT, bool DEFL>
 __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
     constexpr bool kCol = NB >= 4 && NB <= 8;
     constexpr int NV = DEFL ? NP : 2;                    // values of a step's second sum
+    constexpr bool kPeek = !FACT && !DEFL && NB <= 8;    // registers for words and places held ahead
     constexpr int kBlk = kGrp * NB;                      // blocks of S, and distinct columns, of a workgroup
     __shared__ double zs[kBlk][9];                       // the vector's rows this workgroup reads
     __shared__ double part[kGrp][9];
@@ -301,25 +304,38 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
         post(NV);
     };
     // waves 0..3 poll the first half of the values, waves 4..7 the second; a
-    // thread polls one workgroup's words
-    auto collect = [&](int n) {
-        constexpr int kAt = DEFL ? 3 : 1;   // values a poll
-        const int half = wave / 4, j1 = half ? n : (n + 1) / 2;
-        if (G > 1 && (wave % 4) * kWave < G) {   // waves past the last workgroup's words add nothing
-            const int t = tid % kMaxG;
-            const unsigned p = ((((nsum & 1) * kRep + wg % kRep) * NP * 2) * kMaxG + min(t, G - 1)) * 8u;
+    // thread polls one workgroup's words.  peek_sums: the first poll's loads,
+    // ahead of work that needs no sum
+    constexpr int kAt = DEFL ? 3 : 1;      // values a poll
+    u64 wp[kPeek ? kAt : 1][2];
+    const int half = wave / 4, tw = tid % kMaxG;
+    const bool polls = G > 1 && (wave % 4) * kWave < G;   // waves past the last workgroup's words add nothing
+    auto peek_sums = [&](int j0, int j1, u64 (*w)[2]) {
+        const unsigned p = ((((nsum & 1) * kRep + wg % kRep) * NP * 2) * kMaxG + min(tw, G - 1)) * 8u;
+#pragma unroll
+        for (int i = 0; i < kAt; ++i) {
+            const int j = min(j0 + i, j1 - 1);
+            w[i][0] = peek(a.slots, p + (2 * j) * kMaxG * 8u);
+            w[i][1] = peek(a.slots + kMaxG, p + (2 * j) * kMaxG * 8u);
+        }
+    };
+    auto collect = [&](int n, bool peeked) {
+        const int j1 = half ? n : (n + 1) / 2;
+        if (polls) {
+            const int t = tw;
 #pragma unroll 1
             for (int j0 = half * ((n + 1) / 2); j0 < j1; j0 += kAt) {
                 u64 w[kAt][2];
                 int spin = 0;
                 for (;;) {
                     bool ok = true;
+                    if (kPeek && peeked) {
 #pragma unroll
-                    for (int i = 0; i < kAt; ++i) {
-                        const int j = min(j0 + i, j1 - 1);
-                        w[i][0] = peek(a.slots, p + (2 * j) * kMaxG * 8u);
-                        w[i][1] = peek(a.slots + kMaxG, p + (2 * j) * kMaxG * 8u);
+                        for (int i = 0; i < kAt; ++i) { w[i][0] = wp[kPeek ? i : 0][0]; w[i][1] = wp[kPeek ? i : 0][1]; }
+                    } else {
+                        peek_sums(j0, j1, w);
                     }
+                    peeked = false;
 #pragma unroll
                     for (int i = 0; i < kAt; ++i)
                         ok = ok && (unsigned)(w[i][0] >> 32) == nsum && (unsigned)(w[i][1] >> 32) == nsum;
@@ -340,16 +356,19 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
     // Own value v of a vector out to the other workgroups, and the rows this
     // workgroup reads into zs.  nvec numbers the iterations' exchanges.
     // Two values a thread at once (more would not fit the registers).
-    auto receive = [&](int u0, const u64* lo, const u64* hi) {
-        constexpr int kEx = 2;
-        const int n = nc * 9;
-        unsigned at[kEx];
-        u64 w[kEx][2];
+    constexpr int kEx = 2;
+    auto places = [&](int u0, unsigned* at) {
 #pragma unroll
         for (int i = 0; i < kEx; ++i) {
-            const int u = u0 + i * BS < n ? u0 + i * BS : u0;
+            const int u = u0 + i * BS < nc * 9 ? u0 + i * BS : min(u0, nc * 9 - 1);
             at[i] = (unsigned)(scol[u / 9] * 9 + u % 9) * 8u;
         }
+    };
+    unsigned at0[kPeek ? kEx : 1];   // of the first round, which is the only one up to 113 columns
+    if constexpr (kPeek) places(tid, at0);
+    auto receive = [&](int u0, const unsigned* at, const u64* lo, const u64* hi) {
+        const int n = nc * 9;
+        u64 w[kEx][2];
         int spin = 0;
         for (;;) {
             bool ok = true;
@@ -366,17 +385,29 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
             if (u < n) (&zs[0][0])[u] = join(w[i][0], w[i][1]);
         }
     };
-    auto exchange = [&](double v, u64* lo, u64* hi) {
+    auto send = [&](double v, u64* lo, u64* hi) {
+        if (G > 1 && own) put(lo, hi, (unsigned)o * 8u, v, nvec);
+    };
+    auto take = [&](double v, u64* lo, u64* hi) {
         if (G == 1) {
             if (own) zs[lr][ci] = v;   // the column list is all rows
             __syncthreads();
             return true;
         }
-        if (own) put(lo, hi, (unsigned)o * 8u, v, nvec);
+        if constexpr (kPeek)
+            if (tid < nc * 9) receive(tid, at0, lo, hi);
 #pragma unroll 1
-        for (int u = tid; u < nc * 9; u += 2 * BS) receive(u, lo, hi);
+        for (int u = tid + (kPeek ? kEx * BS : 0); u < nc * 9; u += kEx * BS) {
+            unsigned at[kEx];
+            places(u, at);
+            receive(u, at, lo, hi);
+        }
         __syncthreads();
         return s_bad == 0;
+    };
+    auto exchange = [&](double v, u64* lo, u64* hi) {
+        send(v, lo, hi);
+        return take(v, lo, hi);
     };
     // Sum of the partial results of lane groups g0 .. g1 - 1, in order
     auto group_sum = [&](int g0, int g1) {
@@ -422,7 +453,8 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
     __syncthreads();
     for (;;) {
         // S z: the product needs no scalar, so it goes before the sums of the
-        // previous step are collected
+        // previous step are collected, whose words are asked for now
+        if (kPeek && k > 0 && polls) peek_sums(half * ((NV + 1) / 2), half ? NV : (NV + 1) / 2, wp);
         double y = 0.0;
         if (kCol) {
             double acc[9];
@@ -456,7 +488,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
         __syncthreads();
         const double s = own ? group_sum(gs[lr], gs[lr + 1]) : 0.0;
         if (k > 0) {
-            if (!collect(NV)) { fine = false; break; }
+            if (!collect(NV, kPeek)) { fine = false; break; }
             rz_old = rz;
             rz = total(0);
             rr = total(1);
@@ -492,7 +524,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
         q = (k == 0 ? s : s + beta * q) - swm;
         d = (k == 0 ? z : z + beta * d) - wm;
         publish1(d * q);   // has a barrier between the last read of shw and its reuse
-        if (!collect(1)) { fine = false; break; }
+        if (!collect(1, false)) { fine = false; break; }
         const double dq = total(0);
         if (!(dq > 0.0)) {
             if (wg == 0 && tid == 0) { a.state[0] = 1; a.state[2] = BA_ERR_NOT_SPD; a.state[3] = k; }
@@ -516,8 +548,271 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
                 for (int c = 0; c < 9; ++c) z += sM[FACT ? 0 : lr][ci * 9 + c] * sr[FACT ? 0 : lr][c];
             }
         }
+        // z goes out before the sums are formed, so that it has arrived, or is
+        // nearly there, at the first poll (a poll that misses costs another trip)
+        send(z, a.zlo, a.zhi);
         publish2(r, z);
-        if (!exchange(z, a.zlo, a.zhi)) { fine = false; break; }
+        if (!take(z, a.zlo, a.zhi)) { fine = false; break; }
+        ++k;
+    }
+    if (!fine) {
+        if (tid == 0) a.state[4] = 1;
+        return;
+    }
+    if (own) a.out[o] = x;
+    stamp_now(a.stamp);
+}
+
+// The solve in the order of sums of kernels_pcg.hip's kernels A and B (FULL
+// product, block-diagonal M, no deflation), bit for bit, for solves whose
+// result hangs on that order (run_pcg).  A wave owns a row, as in kernel A:
+// lane group g holds the row's entries g, g + 7, ... by rows and lanes 0..8 add
+// the seven groups in order, then hold the row's entries of the vectors.  d^T q
+// goes out by four rows (a workgroup of kernel A), r^T z and r^T r by 28 rows (one
+// of kernel B): the workgroup that owns the first of these takes r and z of all
+// 28 from the exchange and adds them.  All sums run over the same trees.
+//   Against the kernel above: rows fixed to eight a workgroup, nine LDS reads a
+// block, two vectors exchanged and the second sum behind one more trip: 7.8 us
+// an iteration against 6.6 on the 2,000-camera block, 6.4 against 4.7 on 300
+// cameras, where one kernel per phase takes 16.8 and 11.
+constexpr int kOrdRows = NW;   // rows of a workgroup
+constexpr int kOrdB = 28;      // rows of a partial of the second sum
+
+template <int NB>
+__global__ __launch_bounds__(BS) void k_pcg_ord(int n_rows, ChipArgs a) {
+    __shared__ double zs[kGrp * NB][9];
+    __shared__ double sM[kOrdRows][81];
+    __shared__ double sr[kOrdRows][9];
+    __shared__ double part[kOrdRows][GRPW][9];
+    __shared__ double sh[2][NW], sq[2 * 4];
+    __shared__ int scol[kGrp * NB];
+    __shared__ int16_t slc[kGrp * NB];
+    __shared__ int s_bad;
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int G = gridDim.x, wg = blockIdx.x;
+    const int row = wg * kOrdRows + wave;
+    const int c0 = a.cptr[wg], nc = a.cptr[wg + 1] - c0;
+    const int n_a = (n_rows + 3) / 4, n_b = (n_rows + kOrdB - 1) / kOrdB;   // partials of the two sums
+    for (int u = tid; u < nc; u += BS) scol[u] = a.cols[c0 + u];
+    if (tid == 0) s_bad = 0;
+    __syncthreads();
+    const int grp = lane / 9, comp = lane % 9;
+    const bool live = row < n_rows, own = live && lane < 9;
+    const int64_t o = (int64_t)row * 9 + comp;
+    double b[NB][9];
+    int n_own = 0;   // entries of this lane's group
+    const int sg = (wave * GRPW + min(grp, GRPW - 1)) * NB;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+        for (int c = 0; c < 9; ++c) b[j][c] = 0.0;
+        if (live && grp < GRPW) {
+            const int e = a.sf_ptr[row] + grp + j * GRPW;
+            if (e < a.sf_ptr[row + 1]) {
+                const int src = a.sf_src[e];
+                const double* B = a.blk + (int64_t)(src >> 1) * 81;
+                const int base = (src & 1) ? comp : comp * 9, step = (src & 1) ? 9 : 1;
+#pragma unroll
+                for (int c = 0; c < 9; ++c) {
+                    const double v = B[base + c * step];
+                    b[j][c] = a.s32 ? (double)(float)v : v;
+                }
+                if (comp == 0) slc[sg + j] = (int16_t)find_col(scol, nc, a.sf_col[e]);
+                n_own = j + 1;
+            }
+        }
+    }
+    double x = 0.0, r = 0.0, z = 0.0, q = 0.0, d = 0.0;
+    if (own) { x = a.x[o]; r = a.r[o]; z = a.z[o]; }
+    for (int u = tid; u < nc * 9; u += BS) zs[u / 9][u % 9] = a.z[(int64_t)scol[u / 9] * 9 + u % 9];
+    if (live)
+        for (int u = lane; u < 81; u += kWave) sM[wave][u] = a.M[(int64_t)row * 81 + u];
+    // a sum over partials p(i), i < n: thread i < 256 adds i, i + 256, ..., then
+    // the tree of its wave, then the four waves in order (sum_partials)
+    auto over_waves = [&](int j) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) t += sq[j * 4 + w];
+        return t;
+    };
+    if (wave < 4)
+        for (int j = 0; j < 2; ++j) {
+            double s = 0.0;
+            for (int i = tid; i < a.n_part; i += 256) s += a.pR[(int64_t)i * NP + j];
+            s = wave_sum(s);
+            if (lane == 0) sq[j * 4 + wave] = s;
+        }
+    __syncthreads();
+    double rz = over_waves(0), rr = over_waves(1), rz_old = 1.0;
+    const double r0sq = rr;
+    // words of partial i of sum j (0: d^T q, 1: r^T z, 2: r^T r)
+    auto slot = [&](int rep, int j, int i) { return (unsigned)(((rep * 3 + j) * 2 * 2 * kMaxG) + i) * 8u; };
+    u64* const hi_slots = a.slots + 2 * kMaxG;
+    // the values of two words, polled together
+    auto poll = [&](const u64* lo0, const u64* hi0, unsigned at0, const u64* lo1, const u64* hi1, unsigned at1, unsigned ep,
+                    double& v0, double& v1) {
+        int spin = 0;
+        for (;;) {
+            const u64 w[4] = {peek(lo0, at0), peek(hi0, at0), peek(lo1, at1), peek(hi1, at1)};
+            v0 = join(w[0], w[1]);
+            v1 = join(w[2], w[3]);
+            if ((unsigned)(w[0] >> 32) == ep && (unsigned)(w[1] >> 32) == ep && (unsigned)(w[2] >> 32) == ep &&
+                (unsigned)(w[3] >> 32) == ep)
+                return;
+            if (++spin > kSpin) { s_bad = 1; return; }
+        }
+    };
+    const int myrep = wg % kRep;
+    // places of this thread's first two values of z
+    auto place = [&](int u) { return (unsigned)(scol[u / 9] * 9 + u % 9) * 8u; };
+    const bool two = tid + BS < nc * 9;
+    unsigned p0 = 0, p1 = 0;
+    if (tid < nc * 9) {
+        p0 = place(tid);
+        p1 = two ? place(tid + BS) : p0;
+    }
+    unsigned step = 0;   // numbers the words of an iteration
+    int k = 0;
+    bool fine = true;
+    __syncthreads();
+    for (;;) {
+        // S z
+        double y = 0.0;
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (j < n_own) {
+                const double* v = zs[slc[sg + j]];
+#pragma unroll
+                for (int c = 0; c < 9; ++c) y += b[j][c] * v[c];
+            }
+        if (grp < GRPW) part[wave][grp][comp] = y;
+        wave_lds_sync();
+        double s = 0.0;
+        if (own) {
+            s = part[wave][0][comp];
+#pragma unroll
+            for (int g = 1; g < GRPW; ++g) s += part[wave][g][comp];
+        }
+        if (k > 0) {
+            if (wave < 4) {   // n_b <= 74
+                double t0 = 0.0, t1 = 0.0;
+                if (tid < n_b) {
+                    double v0, v1;
+                    poll(a.slots, hi_slots, slot(myrep, 1, tid), a.slots, hi_slots, slot(myrep, 2, tid), step, v0, v1);
+                    t0 += v0;
+                    t1 += v1;
+                }
+                t0 = wave_sum(t0);
+                t1 = wave_sum(t1);
+                if (lane == 0) { sq[wave] = t0; sq[4 + wave] = t1; }
+            }
+            __syncthreads();
+            if (s_bad) { fine = false; break; }
+            rz_old = rz;
+            rz = over_waves(0);
+            rr = over_waves(1);
+        }
+        const bool conv = (rr == 0.0) || (sqrt(rr) <= a.tol * sqrt(r0sq));
+        if (conv || k >= a.max_iter) {
+            if (wg == 0 && tid == 0) {
+                a.state[0] = 1;
+                a.state[2] = conv ? BA_OK : BA_ERR_NOT_CONVERGED;
+                a.state[3] = k;
+                a.scal[1] = r0sq > 0.0 ? sqrt(rr / r0sq) : 0.0;
+            }
+            break;
+        }
+        const double beta = k == 0 ? 0.0 : rz / rz_old;
+        q = k == 0 ? s : s + beta * q;
+        d = k == 0 ? z : z + beta * d;
+        ++step;
+        double dqr = 0.0;
+        if (own) dqr += d * q;
+        dqr = wave_sum(dqr);
+        if (lane == 0) sh[0][wave] = dqr;
+        __syncthreads();   // also: every wave has read sq
+        if (tid < 2 * kRep) {
+            const int h = tid % 2, i = wg * 2 + h;
+            double t = 0.0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) t += sh[0][h * 4 + w];
+            if (i < n_a) put(a.slots, hi_slots, slot(tid / 2, 0, i), t, step);
+        }
+        if (wave < 4) {
+            double t = 0.0;
+            if (tid < n_a) {   // n_a <= 512
+                double v0, v1;
+                poll(a.slots, hi_slots, slot(myrep, 0, tid), a.slots, hi_slots,
+                     slot(myrep, 0, tid + 256 < n_a ? tid + 256 : tid), step, v0, v1);
+                t += v0;
+                if (tid + 256 < n_a) t += v1;
+            }
+            t = wave_sum(t);
+            if (lane == 0) sq[wave] = t;
+        }
+        __syncthreads();
+        if (s_bad) { fine = false; break; }
+        const double dq = over_waves(0);
+        if (!(dq > 0.0)) {
+            if (wg == 0 && tid == 0) { a.state[0] = 1; a.state[2] = BA_ERR_NOT_SPD; a.state[3] = k; }
+            break;
+        }
+        const double alpha = rz / dq;
+        x += alpha * d;
+        r -= alpha * q;
+        if (own) {
+            sr[wave][comp] = r;
+            put(a.rlo, a.rhi, (unsigned)o * 8u, r, step);
+        }
+        wave_lds_sync();
+        if (own) {
+            double t = 0.0;
+#pragma unroll
+            for (int c = 0; c < 9; ++c) t += sM[wave][comp * 9 + c] * sr[wave][c];
+            z = t;
+            put(a.zlo, a.zhi, (unsigned)o * 8u, z, step);
+        }
+        // the second sum's partials whose first row this workgroup owns (at most one)
+        const int pb = (wg * kOrdRows + kOrdB - 1) / kOrdB;
+        if (pb < n_b && pb * kOrdB < (wg + 1) * kOrdRows) {
+            if (wave < 4) {
+                const int at = pb * kOrdB * 9 + tid;
+                const bool act = tid < kOrdB * 9 && at < n_rows * 9;
+                double s0 = 0.0, s1 = 0.0;
+                if (act) {
+                    double zt, rt;
+                    poll(a.zlo, a.zhi, (unsigned)at * 8u, a.rlo, a.rhi, (unsigned)at * 8u, step, zt, rt);
+                    s0 += rt * zt;
+                    s1 += rt * rt;
+                }
+                s0 = wave_sum(s0);
+                s1 = wave_sum(s1);
+                if (lane == 0) { sh[0][4 + wave] = s0; sh[1][4 + wave] = s1; }
+            }
+            __syncthreads();
+            if (tid < 2 * kRep) {
+                const int j = tid % 2;
+                double t = 0.0;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) t += sh[j][4 + w];
+                put(a.slots, hi_slots, slot(tid / 2, 1 + j, pb), t, step);
+            }
+        }
+        double v0, v1;
+        if (tid < nc * 9) {
+            poll(a.zlo, a.zhi, p0, a.zlo, a.zhi, p1, step, v0, v1);
+            (&zs[0][0])[tid] = v0;
+            if (two) (&zs[0][0])[tid + BS] = v1;
+        }
+#pragma unroll 1
+        for (int u = tid + 2 * BS; u < nc * 9; u += 2 * BS) {   // more than 113 columns
+            const int u1 = u + BS < nc * 9 ? u + BS : u;
+            poll(a.zlo, a.zhi, place(u), a.zlo, a.zhi, place(u1), step, v0, v1);
+            (&zs[0][0])[u] = v0;
+            (&zs[0][0])[u1] = v1;
+        }
+        __syncthreads();
+        if (s_bad) { fine = false; break; }
         ++k;
     }
     if (!fine) {
@@ -548,9 +843,9 @@ const void* chip_kernel(int nb, bool fact, bool defl) {
 }  // namespace
 
 // The plan of the on-chip solve from the rows of both triangles (host):
-// contiguous rows per workgroup, as few blocks per lane group as possible
-// (NB) with at most one workgroup per CU; a system that fits one workgroup
-// takes one (its sums need no exchange).  G = 0: the system does not fit.
+// contiguous rows per workgroup, NB blocks per lane group, at most one
+// workgroup per CU; a system that fits one workgroup takes one (its sums need
+// no exchange).  G = 0: the system does not fit.
 void plan_chip(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P) {
     P = ChipPlan();
     const int most = std::min(kMaxG, n_cu);
@@ -572,9 +867,18 @@ void plan_chip(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_c
     };
     if (n_rows <= 0 || sf_ptr[n_rows] > (int64_t)kCap * most) return;
     std::vector<int32_t> brow;
+    // One workgroup where it holds all rows, with the fewest blocks a lane group
+    // that do.  Else as few workgroups as the product leaves cheap: a sum's and
+    // an exchange's latency grows with the workgroups whose words are polled,
+    // the product's time with the blocks a group, steeply from 11 (spills) on.
+    // Least blocks a group 1, 2, 4, 6, 8: 100 cameras 5.88, 4.95, 4.80, 4.74,
+    // 5.01 us an iteration; 300 cameras 6.13, 6.13, 5.25, 5.06, 5.28; 500
+    // cameras of a partition 6.71, 6.71, 6.23, 5.85, 5.94; 700 cameras 6.03,
+    // 6.03, 6.02, 5.72, 5.53; 84 rows of shared intrinsics 5.26, 5.26, 5.03,
+    // 4.90, 5.15; 300 cameras, FSAI 12.0, 11.9, 11.0, 10.9, 12.8.
     for (int one = 1; one >= 0 && P.NB == 0; --one)
         for (int nb : {1, 2, 4, 6, 8, kMaxNB})
-            if (cut(nb, brow) && (!one || brow.size() == 2)) {
+            if ((one || nb >= 6) && cut(nb, brow) && (!one || brow.size() == 2)) {
                 P.NB = nb;
                 break;
             }
@@ -629,7 +933,56 @@ bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, dou
     return e == hipSuccess;
 }
 
+// The plan of the solve in the other kernels' order: eight rows a workgroup,
+// their entries dealt to seven lane groups a row.  G = 0: it does not fit.
+void plan_chip_ordered(int n_rows, const int32_t* sf_ptr, const int32_t* sf_col, int n_cu, ChipPlan& P) {
+    P = ChipPlan();
+    int most = 0;
+    for (int r = 0; r < n_rows; ++r) most = std::max(most, sf_ptr[r + 1] - sf_ptr[r]);
+    const int G = (n_rows + kOrdRows - 1) / kOrdRows;
+    if (n_rows <= 0 || G > std::min(kMaxG, n_cu) || most > GRPW * kMaxNB) return;
+    P.G = G;
+    for (int nb : {kMaxNB, 8, 6, 4})
+        if (most <= GRPW * nb) P.NB = nb;
+    P.cptr.assign(1, 0);
+    std::vector<int32_t> seen(n_rows, -1);
+    for (int g = 0; g < G; ++g) {
+        const size_t c0 = P.cols.size();
+        for (int32_t e = sf_ptr[g * kOrdRows]; e < sf_ptr[std::min(n_rows, (g + 1) * kOrdRows)]; ++e)
+            if (seen[sf_col[e]] != g) {
+                seen[sf_col[e]] = g;
+                P.cols.push_back(sf_col[e]);
+            }
+        std::sort(P.cols.begin() + c0, P.cols.end());
+        P.cptr.push_back((int32_t)P.cols.size());
+    }
+}
+
+bool launch_chip_ordered(ba_ctx* c, const double* M, int n_part, double tol, int max_iter, double* out) {
+    const Chip& H = c->chip_ord;
+    const Pcg& P = c->pcg;
+    ChipArgs a{};
+    a.max_iter = max_iter; a.n_part = n_part; a.s32 = c->s32; a.tol = tol;
+    a.cptr = H.cptr; a.cols = H.cols;
+    a.sf_ptr = c->sf_ptr; a.sf_col = c->sf_col; a.sf_src = c->sf_src;
+    a.blk = c->blk; a.M = M;
+    a.x = P.x; a.r = P.r[0]; a.z = P.z; a.pR = P.pR;
+    a.out = out; a.state = P.state; a.scal = P.scal; a.stamp = c->h_stamp + kStBack;
+    a.zlo = (u64*)P.u; a.zhi = (u64*)P.q; a.rlo = (u64*)P.d; a.rhi = (u64*)P.r[1]; a.slots = (u64*)P.pE;
+    const void* k = H.NB == 4   ? (const void*)k_pcg_ord<4>
+                    : H.NB == 6 ? (const void*)k_pcg_ord<6>
+                    : H.NB == 8 ? (const void*)k_pcg_ord<8>
+                                : (const void*)k_pcg_ord<kMaxNB>;
+    int n_rows = c->n_rows;
+    void* args[] = {&n_rows, &a};
+    const hipError_t e = H.G == 1 ? hipLaunchKernel(k, dim3(1), dim3(BS), args, 0, c->stream)
+                                  : hipLaunchCooperativeKernel(k, dim3(H.G), dim3(BS), args, 0, c->stream);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+}
+
 // Words that the set-up clears for launch_chip
 int64_t chip_slot_words() { return (int64_t)2 * kRep * NP * 2 * kMaxG; }
+static_assert(kRep * 3 * 4 * kMaxG <= 2 * kRep * NP * 2 * kMaxG, "the ordered solve's words are among them");
 
 }  // namespace ba

@@ -598,7 +598,7 @@ __global__ __launch_bounds__(NW * kWave) void k_diag(int n_rows, const int32_t* 
             for (int c = r; c < 9; ++c, ++m) A[m] += jc[r] * q0[c] + jc[9 + r] * q1[c];
         }
     }
-    sred[wv][lane] = wave_sums64(A);   // the wave's 63 sums
+    sred[wv][wave_sums64_at(lane)] = wave_sums64(A);   // the wave's 63 sums
     __syncthreads();
     auto total = [&](int m) {   // value m over the waves, in order
         double t = sred[0][m];
