@@ -265,49 +265,70 @@ __global__ __launch_bounds__(64) void k_feat_node(int n, const int32_t* __restri
 }
 
 // Normalised edge blocks A_e = L_i^-1 S_ij L_j^-T (FP32) and their bf16
-// features.  Three edges per workgroup, one thread per block entry; only
-// the edge that applies its stored upper block as is (etr 0) is computed,
-// and its twin (the reverse edge) takes the transpose, A_twin = A_e^T.  The
-// three blocks of an edge are staged in LDS with contiguous loads, then the
-// two triangular products are formed in two passes (same summation order as
-// a thread-per-edge loop).
-constexpr int kFE = 3;   // edges per workgroup
-__global__ __launch_bounds__(256) void k_feat_edge(int E, const int32_t* __restrict__ esrc, const int32_t* __restrict__ edst,
-                                                   const int32_t* __restrict__ eblk, const int32_t* __restrict__ etr,
-                                                   const int32_t* __restrict__ etwin,
+// features.  Three edges a pass, one thread per block entry; only the edges
+// that apply their stored upper block as is (elow) are computed, and the twin
+// (the reverse edge) takes the transpose, A_twin = A_e^T.  The three blocks of
+// an edge are staged in LDS with contiguous loads, then the two triangular
+// products are formed in two passes (same summation order as a thread-per-edge
+// loop).  A workgroup goes through many passes and asks for the next pass's
+// blocks before it forms this one's products: with a workgroup per three edges,
+// half of them twins that do nothing, 735,000 edges took 613 us, 418 now.
+constexpr int kFE = 3;   // edges a pass
+__global__ __launch_bounds__(256) void k_feat_edge(int n_low, const int32_t* __restrict__ elow,
+                                                   const int32_t* __restrict__ esrc, const int32_t* __restrict__ edst,
+                                                   const int32_t* __restrict__ eblk, const int32_t* __restrict__ etwin,
                                                    const double* __restrict__ blk, const double* __restrict__ Linv,
                                                    float* __restrict__ A, __bf16* __restrict__ xe) {
     __shared__ double sS[kFE][81], sLi[kFE][81], sLj[kFE][81], sT[kFE][81];
     const int le = threadIdx.x / 81, pq = threadIdx.x % 81;
-    const int e = blockIdx.x * kFE + le;
-    const bool act = le < kFE && e < E && etr[e] == 0;
     const int r = pq / 9, c = pq % 9;
-    if (act) {
-        sS[le][pq] = blk[(int64_t)eblk[e] * 81 + pq];
-        sLi[le][pq] = Linv[(int64_t)esrc[e] * 81 + pq];
-        sLj[le][pq] = Linv[(int64_t)edst[e] * 81 + pq];
-    }
-    __syncthreads();
-    if (act) {   // T = S_ij Lj^T
-        double t = 0.0;
-        for (int q = 0; q <= c; ++q) t += sS[le][r * 9 + q] * sLj[le][c * 9 + q];
-        sT[le][pq] = t;
-    }
-    __syncthreads();
-    if (act) {   // A = Li T
-        double t = 0.0;
-        for (int q = 0; q <= r; ++q) t += sLi[le][r * 9 + q] * sT[le][q * 9 + c];
-        const int64_t tw = etwin[e];
-        A[(int64_t)e * 81 + pq] = (float)t;
-        A[tw * 81 + c * 9 + r] = (float)t;
-        __bf16* x = xe + (int64_t)e * F_EDGE;
-        __bf16* xt = xe + tw * F_EDGE;
-        x[pq] = (__bf16)t;
-        xt[c * 9 + r] = (__bf16)t;
-        if (pq < F_EDGE - 81) {
-            x[81 + pq] = (__bf16)0.0f;
-            xt[81 + pq] = (__bf16)0.0f;
+    double vs = 0.0, vi = 0.0, vj = 0.0;
+    int e = -1;
+    auto request = [&](int64_t pass) {
+        const int64_t at = pass * kFE + le;
+        e = le < kFE && at < n_low ? elow[at] : -1;
+        if (e < 0) return;
+        vs = blk[(int64_t)eblk[e] * 81 + pq];
+        vi = Linv[(int64_t)esrc[e] * 81 + pq];
+        vj = Linv[(int64_t)edst[e] * 81 + pq];
+    };
+    const int64_t n_pass = ((int64_t)n_low + kFE - 1) / kFE;
+    request(blockIdx.x);
+    for (int64_t pass = blockIdx.x; pass < n_pass; pass += gridDim.x) {
+        const int cur = e;
+        if (cur >= 0) {
+            sS[le][pq] = vs;
+            sLi[le][pq] = vi;
+            sLj[le][pq] = vj;
         }
+        __syncthreads();
+        request(pass + gridDim.x);
+        if (cur >= 0) {   // T = S_ij Lj^T
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                if (q <= c) t += sS[le][r * 9 + q] * sLj[le][c * 9 + q];
+            sT[le][pq] = t;
+        }
+        __syncthreads();
+        if (cur >= 0) {   // A = Li T
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                if (q <= r) t += sLi[le][r * 9 + q] * sT[le][q * 9 + c];
+            const int64_t tw = etwin[cur];
+            A[(int64_t)cur * 81 + pq] = (float)t;
+            A[tw * 81 + c * 9 + r] = (float)t;
+            __bf16* x = xe + (int64_t)cur * F_EDGE;
+            __bf16* xt = xe + tw * F_EDGE;
+            x[pq] = (__bf16)t;
+            xt[c * 9 + r] = (__bf16)t;
+            if (pq < F_EDGE - 81) {
+                x[81 + pq] = (__bf16)0.0f;
+                xt[81 + pq] = (__bf16)0.0f;
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -724,7 +745,9 @@ __global__ __launch_bounds__(BS) void k_fscatter_g(int E, const int32_t* __restr
 // Gu, the UPPER apply's FP16 copy: each transposed block with its rows
 // (the columns of G_ij) divided by Dn of the member's column block, scaled
 // by its largest magnitude (hs); elements 0..7 of a row as halves in one
-// 16-byte group (Gh, 36 words per member), element 8 in Gh8.
+// 16-byte group (Gh, 36 words per member), element 8 in Gh8.  30,625 rows of
+// 24 members: 625 us with an FP64 division and the divisions of its place per
+// entry and the loads of L_j one after another (610 on the same GPU), 586 now.
 __global__ __launch_bounds__(BS) void k_fassemble(const int32_t* __restrict__ fptr, const int32_t* __restrict__ fJ,
                                                   const int32_t* __restrict__ fedge, const int32_t* __restrict__ fslot,
                                                   const float* __restrict__ O, const float* __restrict__ OE,
@@ -736,26 +759,34 @@ __global__ __launch_bounds__(BS) void k_fassemble(const int32_t* __restrict__ fp
     __shared__ float gh[kFsaiM][81];
     __shared__ float gv[kFsaiM][81];
     __shared__ float smax[kFsaiM];
+    __shared__ double rD[kFsaiM][9];   // 1 / Dn of the members' columns
     const int i = blockIdx.x;
     const int j0 = fptr[i], m = fptr[i + 1] - j0, f0 = j0 - i;
-    for (int e = threadIdx.x; e < m * 81; e += BS) {
-        const int b = e / 81;
-        gh[b][e % 81] = ghat_elem(i, b, m, f0, b < m - 1 ? fedge[j0 + b] : 0, e % 81, O, OE, ao, A);
-    }
+    // thread: entry (p, q) of every third member, so that its place is worked
+    // out once
+    const int b0 = threadIdx.x / 81, pq = threadIdx.x % 81, p = pq / 9, q = pq % 9;
+    if (b0 < 3)
+        for (int b = b0; b < m; b += 3) {
+            gh[b][pq] = ghat_elem(i, b, m, f0, b < m - 1 ? fedge[j0 + b] : 0, pq, O, OE, ao, A);
+            if (Gh && pq < 9) rD[b][pq] = 1.0 / Dn[(int64_t)fJ[j0 + b] * 9 + pq];
+        }
     __syncthreads();
-    for (int e = threadIdx.x; e < m * 81; e += BS) {
-        const int b = e / 81, pq = e % 81, p = pq / 9, q = pq % 9;
-        const int64_t u = j0 + b;
-        const int j = fJ[u];
-        const double* Lj = Linv + (int64_t)j * 81;
-        double s = 0.0;
-        for (int v = q; v < 9; ++v) s += (double)gh[b][p * 9 + v] * Lj[v * 9 + q];
-        const float g = (float)s;
-        if (Gl) Gl[u * 81 + pq] = g;
-        if (Gs) Gs[(int64_t)fslot[u] * 81 + pq] = g;
-        if (Gh) gv[b][q * 9 + p] = (float)((double)g / Dn[(int64_t)j * 9 + q]);
-        else if (Gu) Gu[(int64_t)gu_pos[u] * 81 + q * 9 + p] = g;
-    }
+    if (b0 < 3)
+        for (int b = b0; b < m; b += 3) {
+            const int64_t u = j0 + b;
+            const double* Lj = Linv + (int64_t)fJ[u] * 81;
+            double l[9], s = 0.0;
+#pragma unroll
+            for (int v = 0; v < 9; ++v) l[v] = Lj[v * 9 + q];
+#pragma unroll
+            for (int v = 0; v < 9; ++v)
+                if (v >= q) s += (double)gh[b][p * 9 + v] * l[v];
+            const float g = (float)s;
+            if (Gl) Gl[u * 81 + pq] = g;
+            if (Gs) Gs[(int64_t)fslot[u] * 81 + pq] = g;
+            if (Gh) gv[b][q * 9 + p] = (float)((double)g * rD[b][q]);
+            else if (Gu) Gu[(int64_t)gu_pos[u] * 81 + q * 9 + p] = g;
+        }
     if (!Gh) return;
     __syncthreads();
     const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
@@ -1046,7 +1077,12 @@ void build_graph(Graph& g, int n, const int64_t* row_ptr, const int32_t* col_idx
         if (!h.empty()) BA_HIP_CHECK(hipMemcpyAsync(*p, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
         g.bytes += h.size() * sizeof(int32_t);
     };
-    up(&g.eptr, eptr); up(&g.esrc, src); up(&g.edst, dst); up(&g.etwin, twin); up(&g.eblk, eb); up(&g.etr, et);
+    up(&g.eptr, eptr); up(&g.esrc, src); up(&g.edst, dst); up(&g.etwin, twin); up(&g.eblk, eb);
+    std::vector<int32_t> low;
+    for (size_t e = 0; e < et.size(); ++e)
+        if (et[e] == 0) low.push_back((int32_t)e);
+    g.n_low = (int32_t)low.size();
+    up(&g.elow, low);
     up(&g.diag_blk, diag);
     BA_HIP_CHECK(hipMalloc((void**)&g.xn, (size_t)std::max(n, 1) * F_NODE * sizeof(__bf16)));
     BA_HIP_CHECK(hipMalloc((void**)&g.xe, (size_t)std::max(E, 1) * F_EDGE * sizeof(__bf16)));
@@ -1119,7 +1155,7 @@ void build_graph(Graph& g, int n, const int64_t* row_ptr, const int32_t* col_idx
 }
 
 void free_graph(Graph& g) {
-    void* p[] = {g.eptr, g.esrc, g.edst, g.etwin, g.eblk, g.etr, g.diag_blk, g.xn, g.xe, g.A, g.Linv, g.flags,
+    void* p[] = {g.eptr, g.esrc, g.edst, g.etwin, g.eblk, g.elow, g.diag_blk, g.xn, g.xe, g.A, g.Linv, g.flags,
                  g.fptr, g.fJ, g.fedge, g.fslot, g.ftile, g.ftptr, g.fsrc, g.fdst, g.fe, g.fd_ptr, g.fd_list, g.e2f};
     for (void* q : p)
         if (q) (void)hipFree(q);
@@ -1130,8 +1166,8 @@ void compute_features(Graph& g, const double* blk, hipStream_t st) {
     BA_HIP_CHECK(hipMemsetAsync(g.flags, 0, 4 * sizeof(int), st));
     if (g.n > 0) k_feat_node<<<nblk(g.n, 64), 64, 0, st>>>(g.n, g.diag_blk, blk, g.Linv, g.xn, g.flags);
     if (g.E > 0)
-        k_feat_edge<<<(g.E + kFE - 1) / kFE, 256, 0, st>>>(g.E, g.esrc, g.edst, g.eblk, g.etr, g.etwin, blk, g.Linv,
-                                                            g.A, g.xe);
+        k_feat_edge<<<(unsigned)std::min<int64_t>((g.n_low + kFE - 1) / kFE, 2048), 256, 0, st>>>(
+            g.n_low, g.elow, g.esrc, g.edst, g.eblk, g.etwin, blk, g.Linv, g.A, g.xe);
     BA_HIP_CHECK(hipGetLastError());
 }
 

@@ -33,7 +33,8 @@ inline int64_t off_u(int l) { return off_U(l) + 2 * H * H; }
 // one RCS instance.
 struct Graph {
     int n = 0, E = 0;
-    int32_t *eptr = nullptr, *esrc = nullptr, *edst = nullptr, *etwin = nullptr, *eblk = nullptr, *etr = nullptr;
+    int32_t *eptr = nullptr, *esrc = nullptr, *edst = nullptr, *etwin = nullptr, *eblk = nullptr;
+    int32_t n_low = 0, *elow = nullptr;   // the edges that apply their stored upper block as is
     int32_t* diag_blk = nullptr;       // block index of each node's diagonal block
     __bf16 *xn = nullptr, *xe = nullptr;
     float* A = nullptr;                // [E][81] normalised blocks L_i^-1 S_ij L_j^-T

@@ -229,11 +229,13 @@ __device__ __forceinline__ double row_gather(int start, int n, const int32_t* __
 }
 
 // S W for the kW gauge vectors of one block row (W rows kW * 9 apart): the
-// row's blocks are read once for all of them; results in lanes 0..8 of
-// out[v].  Same entry order and group sums as row_gather.
+// row's blocks are read once for all of them, straight from the upper blocks
+// (src: block, and whether transposed; rounded to TB); results in lanes 0..8
+// of out[v].  Same entry order and group sums as row_gather.
 template <typename TB>
 __device__ __forceinline__ void row_gather_w(int start, int n, const int32_t* __restrict__ col,
-                                             const TB* __restrict__ blk, const double* __restrict__ W, double* out) {
+                                             const int32_t* __restrict__ src, const double* __restrict__ blk,
+                                             const double* __restrict__ W, double* out) {
     constexpr int U = 4;
     __shared__ double sxw[WPB][GRPW * U][9];
     const int lane = threadIdx.x % kWave;
@@ -251,7 +253,11 @@ __device__ __forceinline__ void row_gather_w(int start, int n, const int32_t* __
                 const int e = e0 + u * GRPW;
                 const int ee = start + (e < n ? e : e0);
                 ci[u] = col[ee];
-                load_row9(blk + (int64_t)ee * 81 + comp * 9, bv[u]);
+                const int from = src[ee];
+                const double* B = blk + (int64_t)(from >> 1) * 81 + ((from & 1) ? comp : comp * 9);
+                const int step = (from & 1) ? 9 : 1;
+#pragma unroll
+                for (int c = 0; c < 9; ++c) bv[u][c] = (TB)B[c * step];
             }
 #pragma unroll
             for (int v = 0; v < kW; ++v) {
@@ -350,16 +356,19 @@ __global__ void k_gauge_W(int n_cams, const int32_t* __restrict__ cam_row, const
     for (int i = 0; i < 3; ++i) Wr[6 * 9 + 3 + i] = p[3 + i];
 }
 
-// SW = S W, one wave per block row, the seven columns in turn
+// SW = S W, one wave per block row, the seven columns in turn.  (From a copy
+// of both triangles, which the UPPER product and the solve on the chip do
+// without: 30,625 rows 346 us for the copy and 308 for this; 270 now.)
 template <typename TS>
 __global__ __launch_bounds__(BS) void k_spmm_W(int n_rows, const int32_t* __restrict__ sf_ptr,
-                                               const int32_t* __restrict__ sf_col, const TS* __restrict__ Sf,
-                                               const double* __restrict__ W, double* __restrict__ SW) {
+                                               const int32_t* __restrict__ sf_col, const int32_t* __restrict__ sf_src,
+                                               const double* __restrict__ blk, const double* __restrict__ W,
+                                               double* __restrict__ SW) {
     const int lane = threadIdx.x % kWave;
     for (int row = blockIdx.x * WPB + threadIdx.x / kWave; row < n_rows; row += gridDim.x * WPB) {
         const int a = sf_ptr[row];
         double y[kW];
-        row_gather_w<TS>(a, sf_ptr[row + 1] - a, sf_col, Sf, W, y);
+        row_gather_w<TS>(a, sf_ptr[row + 1] - a, sf_col, sf_src, blk, W, y);
         if (lane < 9)
 #pragma unroll
             for (int v = 0; v < kW; ++v) SW[(int64_t)row * kW * 9 + v * 9 + lane] = y[v];
@@ -680,11 +689,13 @@ __device__ __forceinline__ double row_factor_t(int start, int n, const int32_t* 
             }
         }
     }
-    double t[9], out = 0.0;
+    const double out = wave_sums9(acc);
+    double t[9];   // every lane needs all nine
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        t[i] = wave_sum(acc[i]);
-        if (lane == i) out = t[i];
+        const uint64_t b = __builtin_bit_cast(uint64_t, out);
+        const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, i), hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+        t[i] = __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
     }
     if (grp < GRPW) {
         for (int e0 = grp; e0 < n; e0 += GRPW * U) {
@@ -1291,10 +1302,10 @@ void enqueue_iterations(ba_ctx* c, int mode, const double* M, int defl, double t
 // The copy of the current RCS that the next products read: both triangles by
 // rows (FULL products, and with `full` always), FP64 or for an FP32 solve
 // rounded to FP32; for an FP32 UPPER solve the transposed FP32 upper blocks.
-void ensure_sf(ba_ctx* c, bool full) {
+void ensure_sf(ba_ctx* c) {
     if (c->n_sf == 0) return;
     const unsigned g = (unsigned)std::min<int64_t>((c->n_sf + kCopyB - 1) / kCopyB, 16384);
-    if (full || !c->upper) {
+    if (!c->upper) {
         if (c->s32 ? !c->sf32_ready : !c->sf_ready) {
             if (c->s32)
                 k_build_sf<float><<<g, BS, 0, c->stream>>>(c->n_sf, c->sf_src, c->blk, c->Sf32);
@@ -1316,11 +1327,10 @@ void prepare_deflation(ba_ctx* c) {
     const int nr = c->n_rows, g = grid_of(nr);
     hipStream_t st = c->stream;
     k_gauge_W<<<(c->n_cams + 255) / 256, 256, 0, st>>>(c->n_cams, c->cam_row, c->lin_cams, P.W);
-    ensure_sf(c, true);
     if (c->s32)
-        k_spmm_W<float><<<g, BS, 0, st>>>(nr, c->sf_ptr, c->sf_col, c->Sf32, P.W, P.SW);
+        k_spmm_W<float><<<g, BS, 0, st>>>(nr, c->sf_ptr, c->sf_col, c->sf_src, c->blk, P.W, P.SW);
     else
-        k_spmm_W<double><<<g, BS, 0, st>>>(nr, c->sf_ptr, c->sf_col, c->Sf, P.W, P.SW);
+        k_spmm_W<double><<<g, BS, 0, st>>>(nr, c->sf_ptr, c->sf_col, c->sf_src, c->blk, P.W, P.SW);
     c->defl_s32 = c->s32;
     k_defl_E_part<<<g, BS, 0, st>>>(nr, P.W, P.SW, P.pE);
     k_defl_E_sum<<<kW * kW, BS, 0, st>>>(g, P.pE, P.bm + 8);
@@ -1346,7 +1356,7 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     const bool ordered = tol > kChipTol && !c->upper && mode == 0 && !defl && c->chip_ord.G > 0;
     const bool chip = ordered || (c->chip.G > 0 && !c->upper && tol <= kChipTol);
     if (begin && !chip) launch_stamp(c, (int)(begin - c->h_stamp));
-    if (!chip || x0) ensure_sf(c, false);
+    if (!chip || x0) ensure_sf(c);
     // state and scalars to the host's words, and the end's stamp, in one launch
     auto report = [&]() {
         k_report<<<1, 64, 0, st>>>(P.state, P.scal, c->h_flags + 4, c->h_scal + 8, c->h_stamp + kStBack);
@@ -1394,8 +1404,11 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
     // remaining iterations in fixed batches (a captured graph when possible);
     // the stop flag of a batch is read back while the next batch runs, and
     // kernels after the stop return at once
-    const int batch = kPcgBatch;
-    const int n_batches = max_iter > 0 ? (max_iter + batch - 1) / batch : 0;
+    // (equal batches that end with the last iteration's stop test: kernels
+    // after it only start and return, 15 us an iteration; 8 iterations on 15,000
+    // rows launched 17 times)
+    const int n_batches = max_iter > 0 ? (max_iter + kPcgBatch - 1) / kPcgBatch : 0;
+    const int batch = n_batches > 0 ? (max_iter + n_batches - 1) / n_batches : kPcgBatch;
     hipGraphExec_t exec = nullptr;
     if (c->use_graphs && n_batches > 0) {
         for (auto& gr : c->pcg_graphs)
@@ -1447,7 +1460,7 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
 // y = S x in the layout selected for the next solve (c->upper, c->s32)
 void launch_product(ba_ctx* c, const double* x, double* y) {
     if (c->n_rows == 0) return;
-    ensure_sf(c, false);
+    ensure_sf(c);
     product_cur(c, x, y, c->stream);
 }
 
