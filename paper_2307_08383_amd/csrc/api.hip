@@ -359,8 +359,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // by the rows of each of its cameras; inside a compact cluster those rows
     // run close together on one XCD, so the track's records come from L2 / MALL
     // instead of HBM after the first of them.
-    //   Up to kTileMin of records, twice what the MALL holds, a camera
-    // pair's couples stay together and clusters of about 4 MB, an XCD's L2,
+    //   Up to kTileMin of records a camera pair's couples stay together and clusters of about 4 MB, an XCD's L2,
     // order the pairs.  Beyond it the couples are worked through by tiles, the
     // points whose first free row lies in one cluster, of about 1 MB: a pair's
     // couples are ordered by tile and cut between tiles into units, and an XCD
@@ -369,10 +368,14 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // tiles of 4, 2, 1 and 0.5 MB: 15,000 cameras, FP64, 4.8 GB of records: 3,108
     // against 2,835, 2,738, 2,720 and 2,720 us; 18,000 cameras, FP32, 1.7 GB:
     // 1,467 against 1,435, 1,407, 1,404 and 1,407; 2,000 cameras, FP64, 460 MB:
-    // 228 against 228 and (2 MB) 230.
+    // 228 against 228 and (2 MB) 230.  A cut pair's block is summed in another
+    // order, and a long solve may move by more than that order does, so tiles
+    // are for where they give more than a few per cent of the stage.
     const double rec_bytes = (double)kRec * (c->precision == BA_MIXED ? sizeof(float) : sizeof(double));
-    constexpr double kTileMin = 512.0 * (1 << 20);
-    const bool tiled = rec_bytes * (double)n_rec > kTileMin;
+    constexpr double kTileMin = 4.0 * (1 << 30);
+    // (not under a workspace cap, which the cut pairs' partial blocks would count
+    // against: up to 5% of the records there)
+    const bool tiled = rec_bytes * (double)n_rec > kTileMin && c->cap == 0;
     std::vector<int32_t> clus(nr, -1);
     {
         std::vector<int32_t> adj_ptr(nr + 1, 0), adj;

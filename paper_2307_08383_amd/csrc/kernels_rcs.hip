@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kLinNW * kWave) void k_linpoint_d(int n_chunk, cons
 // from 16 different bank quads.
 //   Measured: 15,000 cameras, 57.6 M couples, FP64 3,500 -> 2,660 us with the
 // tiles described where the units are built; 18,000 cameras, 42.4 M couples,
-// FP32 records 1,707 -> 1,371 us; 2,000 cameras, 3.8 M couples, FP64 229 -> 207.
+// FP32 records 1,707 -> 1,450 us; 2,000 cameras, 3.8 M couples, FP64 229 -> 207.
 //   Units are stored by tiles or clusters of cameras (longest first inside
 // each); workgroup b runs on XCD b mod 8, which takes the waves of its own
 // contiguous range of units (ranges of equal work), keeping the records of

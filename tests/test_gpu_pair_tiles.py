@@ -1,5 +1,5 @@
 """The pair stage above and below the size from which its work is ordered and
-cut by tiles of points (512 MiB of records), with two and with three LDS
+cut by tiles of points (4 GiB of records), with two and with three LDS
 buffers (units of fewer and of more than 16 steps), free and fixed cameras
 (needs a GPU): RCS and right-hand side against the oracle."""
 import numpy as np
@@ -17,10 +17,10 @@ ba = pytest.importorskip("paper_2307_08383_amd.ba")
 
 
 @pytest.mark.parametrize("nx,ny,n_pts,n_fixed,precision", [
-    (20, 15, 650_000, 0, 0),       # 500 MB of FP64 records: whole pairs, long units
-    (20, 15, 750_000, 0, 0),       # 576 MB: tiles, long units
-    (50, 40, 750_000, 7, 0),       # tiles, short units
-    (20, 15, 1_500_000, 7, 1),     # 576 MB of FP32 records: tiles
+    (20, 15, 750_000, 0, 0),       # 576 MB of FP64 records: whole pairs, long units
+    (50, 40, 750_000, 7, 0),       # short units
+    (20, 15, 1_500_000, 7, 1),     # 576 MB of FP32 records
+    (60, 50, 5_700_000, 7, 0),     # 4.4 GB: tiles
 ])
 def test_rcs_against_the_oracle(nx, ny, n_pts, n_fixed, precision):
     """About four records a point.  Bounds of the formation tests: blocks
