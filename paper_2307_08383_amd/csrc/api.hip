@@ -364,7 +364,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // points whose first free row lies in one cluster, of about 1 MB: a pair's
     // couples are ordered by tile and cut between tiles into units, and an XCD
     // works on one tile's units at a time, whose records it then reads from HBM
-    // once.  The pair stage and the sums of the cut pairs, start's order against
+    // once.  The pair stage and the sums of the cut pairs, whole pairs against
     // tiles of 4, 2, 1 and 0.5 MB: 15,000 cameras, FP64, 4.8 GB of records: 3,108
     // against 2,835, 2,738, 2,720 and 2,720 us; 18,000 cameras, FP32, 1.7 GB:
     // 1,467 against 1,435, 1,407, 1,404 and 1,407; 2,000 cameras, FP64, 460 MB:
