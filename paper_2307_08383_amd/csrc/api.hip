@@ -794,21 +794,20 @@ double elapsed(const ba_ctx* c, int a, int b) {
     return t1 > t0 ? (double)(t1 - t0) * c->stamp_ms : 0.0;
 }
 
-// point_done: the point stage already ran, fused with the linearization, which
-// ended at stamp kStLinEnd.  end: the stamp that the caller lets follow.
+// point_done: the point stage already ran, fused with the linearization.
+// end: the stamp that the caller lets follow.  The stamps of a formation are
+// written by formations alone: a later linearization leaves its stage times.
 ba_status form_rcs_async(ba_ctx* c, double lambda, bool point_done, int end) {
-    int begin = ba::kStLinEnd, pair = ba::kStLinEnd;
+    const int pair = ba::kStPair, begin = point_done ? pair : ba::kStForm;
     if (!point_done) {
         // flags[2] (records out of range) belongs to the linearization and stays
-        begin = ba::kStForm;
-        pair = ba::kStPair;
         ba::launch_begin(c, 0xfb, {}, {}, begin);
         if (c->shared)   // the point terms need the Jacobians again: one fused pass
             ba::launch_linpoint_shared(c, c->lin_params, c->lin_pts, lambda, nullptr);
         else
             ba::launch_point(c, lambda);
     }
-    ba::launch_offdiag(c, point_done ? nullptr : c->h_stamp + pair);
+    ba::launch_offdiag(c, c->h_stamp + pair);
     if (c->shared) {
         ba::launch_stamp(c, ba::kStDiag);
         ba::launch_node_diag(c, lambda);

@@ -642,7 +642,7 @@ void launch_project(const double* cams, const double* pts, const int32_t* obs_ca
                     int64_t n_obs, const double* noise, double* uv, hipStream_t st);
 // Stamps: kernels take the address of one and write it when their first block
 // starts (the end of a stage is the start of the next, or of a sum's last block)
-enum { kStLin = 0, kStLinEnd, kStForm, kStPair, kStDiag, kStPrep, kStSolve, kStBack, kStEval, kStUpdate, kStEnd, kStSpare, kStCount };
+enum { kStLin = 0, kStLinEnd, kStForm, kStPair, kStDiag, kStPrep, kStSolve, kStBack, kStEval, kStUpdate, kStEnd, kStCount };
 void launch_stamp(ba_ctx* c, int i);
 // Start of a stage: clears flags (bit i of mask: flags[i]), copies up to two
 // arrays and stamps i, in one launch
