@@ -1378,14 +1378,22 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
         launch_factor_init(c, g, defl, st);
     }
     if (chip) {
-        const bool launched = ordered ? launch_chip_ordered(c, M, g, tol, max_iter, out)
-                                      : launch_chip(c, mode, M, defl, g, tol, max_iter, out);
+        // a start that shares memory with the result must survive a solve that
+        // gives up, whose workgroups write what they have
+        const int64_t n = (int64_t)nr * 9;
+        double* const to = x0 && x0 < out + n && out < x0 + n ? P.x : out;
+        const bool launched = ordered ? launch_chip_ordered(c, M, g, tol, max_iter, to)
+                                      : launch_chip(c, mode, M, defl, g, tol, max_iter, to);
         if (launched && !wait) {
             *iters = -1;
             return BA_OK;
         }
         if (launched) report();
         if (launched && !c->h_flags[8]) {
+            if (to != out) {
+                BA_HIP_CHECK(hipMemcpyAsync(out, to, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, st));
+                BA_HIP_CHECK(hipStreamSynchronize(st));
+            }
             *iters = c->h_flags[7];
             *relres = c->h_scal[9];
             return (ba_status)c->h_flags[6];
