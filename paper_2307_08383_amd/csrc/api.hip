@@ -659,6 +659,17 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     upload(c, &c->sf_src, sf_src);
     upload(c, &c->lo_ptr, lo_ptr);
     upload(c, &c->lo_blk, lo_blk);
+    if (c->cap) {
+        // a cap that held the context when its segments' lists (8 bytes each) were
+        // on the device and the plans and slices were not still holds it
+        int64_t spare = 8 * (int64_t)nseg + 4 -
+                        (shared ? 4 * (int64_t)(slice_cam.size() + slice_beg.size() + slice_ptr.size()) : 0);
+        for (ba::ChipPlan* P : {&cp, &co}) {
+            const int64_t need = 4 * (int64_t)(P->brow.size() + P->cptr.size() + P->cols.size());
+            if (need > spare) P->G = 0;
+            if (P->G > 0) spare -= need;
+        }
+    }
     if (cp.G > 0) {
         upload(c, &c->chip.brow, cp.brow);
         upload(c, &c->chip.cptr, cp.cptr);
@@ -841,10 +852,19 @@ size_t n_params(const ba_ctx* c) { return 6 * (size_t)c->n_cams + 5 * (size_t)c-
 // by the layout too (UPPER in FP16) and keeps the limit of 256 MiB.
 void select_solver_matrix(ba_ctx* c, int fp32, int product, bool factorised) {
     c->s32 = fp32 ? 1 : 0;
-    const double full_bytes = (double)c->n_sf * 81 * (c->s32 ? sizeof(float) : sizeof(double));
-    c->upper = (product == BA_PRODUCT_UPPER || (product == BA_PRODUCT_AUTO && full_bytes > (factorised ? 256.0 : 128.0) * (1 << 20))) ? 1 : 0;
+    const double full_bytes = (double)c->n_sf * 81 * (c->s32 ? sizeof(float) : sizeof(double)), MiB = 1 << 20;
+    const bool large = full_bytes > 256.0 * MiB;
+    c->upper = (product == BA_PRODUCT_UPPER ||
+                (product == BA_PRODUCT_AUTO && (large || (!factorised && full_bytes > 128.0 * MiB)))) ? 1 : 0;
     if (c->s32 && !c->Sf32) dalloc(c, &c->Sf32, (size_t)std::max<int64_t>(c->n_sf, 1) * 81);
-    if (c->upper && c->s32 && !c->Su32) dalloc(c, &c->Su32, (size_t)c->n_blk * 81);
+    if (c->upper && c->s32 && !c->Su32) {
+        try {
+            dalloc(c, &c->Su32, (size_t)c->n_blk * 81);
+        } catch (const ba_oom&) {
+            if (product != BA_PRODUCT_AUTO || large) throw;
+            c->upper = 0;   // between the limits FULL does, and needs no second copy
+        }
+    }
 }
 
 void prepare_defl(ba_ctx* c) {

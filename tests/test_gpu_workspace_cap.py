@@ -1,0 +1,68 @@
+"""Contexts under a workspace cap (needs a GPU): caps that held a context
+before it had plans for solves in one kernel still hold it, and a cap that
+held the FULL layout's FP32 copy of S still holds a solve that may choose its
+layout."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2307_08383_amd import scenegen
+
+from gpu_util import T
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+ba = pytest.importorskip("paper_2307_08383_amd.ba")
+
+
+def _create(n_cams, n_pts, cam, pt, uv, cap=0, **kw):
+    return ba.ba_create(n_cams, n_pts, T(cam, torch.int32), T(pt, torch.int32), T(uv, torch.float64), workspace_cap=cap, **kw)
+
+
+# 400 cameras in a chain, point j seen by cameras j and j + 1: 399 segments,
+# whose lists took 3,196 bytes, and plans of 1,768 and 2,204 bytes
+CHAIN_BYTES = 3_548_228
+
+
+def test_context_with_few_neighbours():
+    n = 400
+    pt = np.repeat(np.arange(n - 1), 2)
+    cam = pt + np.tile([0, 1], n - 1)
+    uv = np.zeros((2, 2 * (n - 1)))
+    ctx = _create(n, n - 1, cam, pt, uv, CHAIN_BYTES)
+    try:
+        assert ba.ba_get_sizes(ctx)["device_bytes"] <= CHAIN_BYTES
+    finally:
+        ba.ba_destroy(ctx)
+
+
+def test_fp32_solve_of_a_mid_sized_system():
+    """FULL copy between 128 and 256 MiB: AUTO takes UPPER, whose FP32 copy is
+    another one.  Where the cap has no room for it the solve is FULL's; UPPER
+    by name is refused, and the context goes on."""
+    s = scenegen.aerial_grid_scene(seed=5, nx=125, ny=120, n_pts=300_000, with_stats=False)
+    args = (s.n_cams, s.n_pts, s.obs_cam, s.obs_pt, orc.observations(s))
+    out = []
+    bytes_full = 0
+    for cap in (False, True):
+        ctx = _create(*args, cap=bytes_full if cap else 0)
+        try:
+            ba.ba_linearize(ctx, T(s.cams_init, torch.float64), T(s.pts_init, torch.float64))
+            ba.ba_form_rcs(ctx, 1e-2)
+            sz = ba.ba_get_sizes(ctx)
+            assert 128 << 20 < (2 * sz["n_blk"] - sz["n_rows"]) * 81 * 4 <= 256 << 20
+            x = torch.zeros((sz["n_rows"], 9), dtype=torch.float64, device="cuda")
+            kw = dict(tol=1e-8, max_iter=20, solver_fp32=True)
+            ba.ba_pcg_solve(ctx, x, product=ba.BA_PRODUCT_AUTO if cap else ba.BA_PRODUCT_FULL, **kw)
+            out.append(x.clone())
+            bytes_full = ba.ba_get_sizes(ctx)["device_bytes"]
+            if cap:
+                with pytest.raises(ba.BAError) as ei:
+                    ba.ba_pcg_solve(ctx, x, product=ba.BA_PRODUCT_UPPER, **kw)
+                assert ei.value.status == ba.BA_ERR_OUT_OF_MEMORY
+                ba.ba_pcg_solve(ctx, x, **kw)
+                out.append(x.clone())
+        finally:
+            ba.ba_destroy(ctx)
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
