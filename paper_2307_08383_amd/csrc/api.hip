@@ -302,46 +302,47 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         for (int64_t q = q0; q < q1; ++q)
             for (int32_t a = rptr[q]; a < rptr[q + 1]; ++a) rq[a] = (int32_t)q;
     });
+    // the couples of row r's records in the order of recs; visit gets the
+    // record's place there too
     auto scan_row = [&](int32_t r, const int32_t* recs, auto&& visit) {
         for (int32_t i = 0; i < rowobs_ptr[r + 1] - rowobs_ptr[r]; ++i) {
             const int32_t a = recs[i], q = rq[a];
             for (int32_t b = shared ? rptr[q] : a + 1; b < rptr[q + 1]; ++b) {
                 const int32_t rb = rrow[b];
                 if (rb < 0 || (shared && rb < r)) continue;
-                visit(a, b, rb);
+                visit(i, a, b, rb);
             }
         }
     };
     const int nth = host_threads();
     std::vector<std::vector<int32_t>> t_cnt(nth, std::vector<int32_t>(nr, 0)), t_blk(nth, std::vector<int32_t>(nr));
     std::vector<std::vector<int64_t>> t_pos(nth, std::vector<int64_t>(nr));
-    std::vector<std::vector<int32_t>> t_touch(nth);
-    // the row's columns with their couple counts (t_cnt, t_touch)
-    auto count_row = [&](int32_t r, int t) {
+    std::vector<std::vector<int32_t>> t_touch(nth), t_tile(nth);
+    // each row's segments, by ascending column: column (s >= r) and couples
+    struct Seg { int32_t col, n; };
+    std::vector<std::vector<Seg>> segs(nr);
+    std::vector<int64_t> ctr(nr + 1, 0), row_ptr(nr + 1, 0), row_steps(nr);   // row_steps: of four couples
+    std::vector<int32_t> sptr(nr + 1, 0);
+    parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
         std::vector<int32_t>& cnt_s = t_cnt[t];
         std::vector<int32_t>& touch = t_touch[t];
-        int64_t m = 0;
-        scan_row(r, rowobs.data() + rowobs_ptr[r], [&](int32_t, int32_t, int32_t s) {
-            if (cnt_s[s]++ == 0) touch.push_back(s);
-            ++m;
-        });
-        return m;
-    };
-    std::vector<int64_t> ctr(nr + 1, 0), row_ptr(nr + 1, 0);
-    std::vector<int32_t> sptr(nr + 1, 0);
-    std::vector<std::vector<int32_t>> cols(nr);   // each row's columns s > r, ascending
-    parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
         for (int64_t r = r0; r < r1; ++r) {
-            ctr[r + 1] = count_row((int32_t)r, t);
-            int32_t nb = 1;
-            for (int32_t s2 : t_touch[t]) {
-                if (s2 != r) { ++nb; cols[r].push_back(s2); }
-                t_cnt[t][s2] = 0;
+            int64_t m = 0;
+            scan_row((int32_t)r, rowobs.data() + rowobs_ptr[r], [&](int32_t, int32_t, int32_t, int32_t s2) {
+                if (cnt_s[s2]++ == 0) touch.push_back(s2);
+                ++m;
+            });
+            std::sort(touch.begin(), touch.end());
+            segs[r].reserve(touch.size());
+            for (int32_t s2 : touch) {
+                segs[r].push_back({s2, cnt_s[s2]});
+                row_steps[r] += (cnt_s[s2] + 3) / 4;
+                cnt_s[s2] = 0;
             }
-            std::sort(cols[r].begin(), cols[r].end());
-            sptr[r + 1] = (int32_t)t_touch[t].size();
-            row_ptr[r + 1] = nb;
-            t_touch[t].clear();
+            ctr[r + 1] = m;
+            sptr[r + 1] = (int32_t)touch.size();
+            row_ptr[r + 1] = 1 + (int64_t)touch.size() - (!touch.empty() && touch[0] == r ? 1 : 0);
+            touch.clear();
         }
     });
     for (int32_t r = 0; r < nr; ++r) {
@@ -377,29 +378,28 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // against: up to 5% of the records there)
     const bool tiled = rec_bytes * (double)n_rec > kTileMin && c->cap == 0;
     std::vector<int32_t> clus(nr, -1);
+    int32_t n_cl = 0;
     {
         std::vector<int32_t> adj_ptr(nr + 1, 0), adj;
         for (int32_t r = 0; r < nr; ++r)
-            for (int32_t s2 : cols[r]) {
-                adj_ptr[r + 1]++;
-                adj_ptr[s2 + 1]++;
-            }
+            for (const Seg& g : segs[r])
+                if (g.col != r) {
+                    adj_ptr[r + 1]++;
+                    adj_ptr[g.col + 1]++;
+                }
         for (int32_t r = 0; r < nr; ++r) adj_ptr[r + 1] += adj_ptr[r];
         adj.resize(adj_ptr[nr]);
         {
             std::vector<int32_t> fill(adj_ptr.begin(), adj_ptr.end() - 1);
             for (int32_t r = 0; r < nr; ++r)
-                for (int32_t s2 : cols[r]) {
-                    adj[fill[r]++] = s2;
-                    adj[fill[s2]++] = r;
-                }
+                for (const Seg& g : segs[r])
+                    if (g.col != r) {
+                        adj[fill[r]++] = g.col;
+                        adj[fill[g.col]++] = r;
+                    }
         }
-        std::vector<int64_t> row_obs(nr, 0);
-        for (int64_t k = 0; k < n_rec; ++k)
-            if (rrow[k] >= 0) row_obs[rrow[k]]++;
         const double budget = (tiled ? 1.0 : 4.0) * (1 << 20);
         std::vector<int32_t> queue;
-        int32_t n_cl = 0;
         for (int32_t s0 = 0; s0 < nr; ++s0) {
             if (clus[s0] >= 0) continue;
             queue.assign(1, s0);
@@ -407,7 +407,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
             double bytes = 0.0;
             for (size_t h = 0; h < queue.size() && bytes < budget; ++h) {
                 const int32_t r = queue[h];
-                bytes += (double)row_obs[r] * rec_bytes;
+                bytes += (double)(rowobs_ptr[r + 1] - rowobs_ptr[r]) * rec_bytes;
                 for (int32_t e = adj_ptr[r]; e < adj_ptr[r + 1] && bytes < budget; ++e)
                     if (clus[adj[e]] < 0) {
                         clus[adj[e]] = n_cl;
@@ -428,55 +428,6 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         });
     }
     ph.mark("clusters");
-    std::vector<int32_t> trip(2 * (size_t)ntr), col_idx(row_ptr[nr]);
-    std::vector<int32_t> off_blk(nseg), pair_ptr(nseg + 1), seg_row(nseg);
-    parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
-        std::vector<int32_t> recs;   // the row's records by tile, in record order inside a tile
-        std::vector<int32_t>& cnt_s = t_cnt[t];
-        std::vector<int32_t>& blk_s = t_blk[t];
-        std::vector<int64_t>& pos_s = t_pos[t];
-        std::vector<int32_t>& touch = t_touch[t];
-        for (int64_t r = r0; r < r1; ++r) {
-            count_row((int32_t)r, t);
-            std::sort(touch.begin(), touch.end());
-            int64_t kb = row_ptr[r];
-            col_idx[kb++] = (int32_t)r;
-            for (int32_t s2 : touch) {
-                if (s2 == r) {
-                    blk_s[s2] = (int32_t)row_ptr[r];
-                } else {
-                    blk_s[s2] = (int32_t)kb;
-                    col_idx[kb++] = s2;
-                }
-            }
-            std::stable_sort(touch.begin(), touch.end(), [&](int32_t x, int32_t y) { return cnt_s[x] > cnt_s[y]; });
-            int64_t m = ctr[r];
-            int32_t sg = sptr[r];
-            for (int32_t s2 : touch) {
-                off_blk[sg] = blk_s[s2];
-                seg_row[sg] = (int32_t)r;
-                pair_ptr[sg] = (int32_t)m;
-                pos_s[s2] = m;
-                m += cnt_s[s2];
-                ++sg;
-            }
-            recs.assign(rowobs.begin() + rowobs_ptr[r], rowobs.begin() + rowobs_ptr[r + 1]);
-            if (tiled)
-                std::stable_sort(recs.begin(), recs.end(), [&](int32_t x, int32_t y) { return tile[rq[x]] < tile[rq[y]]; });
-            scan_row((int32_t)r, recs.data(), [&](int32_t a, int32_t b, int32_t s2) {
-                const int64_t d = pos_s[s2]++;
-                trip[2 * d] = a;
-                trip[2 * d + 1] = b;
-            });
-            for (int32_t s2 : touch) cnt_s[s2] = 0;
-            touch.clear();
-        }
-    });
-    pair_ptr[nseg] = (int32_t)ntr;
-    c->n_blk = row_ptr[nr];
-    c->n_offseg = nseg;
-    c->n_pairs = ntr;
-    ph.mark("couples");
     // pair-stage work units.  One lane group works through a unit's couples
     // one after another, so a long segment would set the stage's duration on
     // small problems: segments longer than the cap are cut into chunks that
@@ -487,41 +438,122 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     // cluster or tile the units are ordered longest first (neighbouring
     // units have similar lengths); the waves are then cut into 8 contiguous
     // ranges of equal work, one per XCD.
+    c->unit_steps = 0;
+    for (int32_t r = 0; r < nr; ++r) c->unit_steps += row_steps[r];
+    const int64_t cap = 4 * std::max<int64_t>(8, c->unit_steps / (4 * (256 * 16 * 4)));
+    // Pieces of the segments, row by row: couples [t0, t1) and the window (tile
+    // or cluster) whose units they run with.  Cut while the row's couples are at
+    // hand: looked up again for all couples afterwards, twice, the tiles made the
+    // context of 60,000 cameras and 209 M couples 11% slower to create.
+    struct Piece { int32_t t0, t1, win; };
+    std::vector<std::vector<Piece>> piece(nr);
+    std::vector<int32_t> n_piece(nseg);
+    std::vector<int32_t> trip(2 * (size_t)ntr), col_idx(row_ptr[nr]);
+    std::vector<int32_t> off_blk(nseg), pair_ptr(nseg + 1), seg_row(nseg);
+    parallel_for(nr, 16, [&](int64_t r0, int64_t r1, int t) {
+        std::vector<int32_t>& blk_s = t_blk[t];
+        std::vector<int64_t>& pos_s = t_pos[t];
+        std::vector<int32_t>& tile_n = t_tile[t];
+        std::vector<int32_t> rec_tile, recs, tiles, couple_tile;   // of one row
+        std::vector<Seg> order;
+        if (tiled && tile_n.empty()) tile_n.assign(n_cl, 0);
+        for (int64_t r = r0; r < r1; ++r) {
+            int64_t kb = row_ptr[r];
+            col_idx[kb++] = (int32_t)r;
+            for (const Seg& g : segs[r]) {
+                if (g.col == r) {
+                    blk_s[g.col] = (int32_t)row_ptr[r];
+                } else {
+                    blk_s[g.col] = (int32_t)kb;
+                    col_idx[kb++] = g.col;
+                }
+            }
+            order = segs[r];
+            std::stable_sort(order.begin(), order.end(), [](const Seg& x, const Seg& y) { return x.n > y.n; });
+            int64_t m = ctr[r];
+            int32_t sg = sptr[r];
+            for (const Seg& g : order) {
+                off_blk[sg] = blk_s[g.col];
+                seg_row[sg] = (int32_t)r;
+                pair_ptr[sg] = (int32_t)m;
+                pos_s[g.col] = m;
+                m += g.n;
+                ++sg;
+            }
+            const int32_t* list = rowobs.data() + rowobs_ptr[r];
+            const int32_t n_r = rowobs_ptr[r + 1] - rowobs_ptr[r];
+            if (tiled) {
+                // the row's records by tile, in record order inside a tile
+                // (counting sort; a row's records lie in a few tiles)
+                tiles.clear();
+                rec_tile.resize(n_r);
+                recs.resize(n_r);
+                couple_tile.resize(ctr[r + 1] - ctr[r]);
+                for (int32_t i = 0; i < n_r; ++i) {
+                    rec_tile[i] = tile[rq[list[i]]];
+                    if (tile_n[rec_tile[i]]++ == 0) tiles.push_back(rec_tile[i]);
+                }
+                std::sort(tiles.begin(), tiles.end());
+                int32_t at = 0;
+                for (int32_t w : tiles) {
+                    const int32_t k = tile_n[w];
+                    tile_n[w] = at;
+                    at += k;
+                }
+                for (int32_t i = 0; i < n_r; ++i) recs[tile_n[rec_tile[i]]++] = list[i];
+                int32_t i = 0;   // tile_n holds the tiles' ends now
+                for (int32_t w : tiles) {
+                    for (; i < tile_n[w]; ++i) rec_tile[i] = w;
+                    tile_n[w] = 0;
+                }
+                list = recs.data();
+            }
+            scan_row((int32_t)r, list, [&](int32_t i, int32_t a, int32_t b, int32_t s2) {
+                const int64_t d = pos_s[s2]++;
+                trip[2 * d] = a;
+                trip[2 * d + 1] = b;
+                if (tiled) couple_tile[d - ctr[r]] = rec_tile[i];
+            });
+            // cut where the tile changes, but not into pieces of fewer than kMinRun
+            // couples (four steps; a piece costs a start, a reduction and 1,300
+            // bytes of partial block; 8 and 32 time alike), then by the cap
+            constexpr int64_t kMinRun = 16;
+            const int32_t* tl = couple_tile.data();
+            int64_t a = ctr[r];
+            sg = sptr[r];
+            for (const Seg& g : order) {
+                const size_t before = piece[r].size();
+                const int64_t b = a + g.n;
+                for (int64_t lo = a; lo < b;) {
+                    int64_t hi = b;
+                    int32_t w = clus[r];
+                    if (tiled) {
+                        for (int64_t t = lo + kMinRun; t <= b - kMinRun; ++t)
+                            if (tl[t - ctr[r]] != tl[t - 1 - ctr[r]]) { hi = t; break; }
+                        w = tl[(lo + hi) / 2 - ctr[r]];
+                    }
+                    for (int64_t t = lo; t < hi; t += cap)
+                        piece[r].push_back({(int32_t)t, (int32_t)std::min<int64_t>(t + cap, hi), w});
+                    lo = hi;
+                }
+                n_piece[sg++] = (int32_t)(piece[r].size() - before);
+                a = b;
+            }
+        }
+    });
+    std::vector<std::vector<Seg>>().swap(segs);
+    pair_ptr[nseg] = (int32_t)ntr;
+    c->n_blk = row_ptr[nr];
+    c->n_offseg = nseg;
+    c->n_pairs = ntr;
+    ph.mark("couples");
     std::vector<int32_t> unit_rng, unit_dst, lseg_blk, lseg_ptr{0};
     {
         struct Unit { int32_t win, t0, t1, dst; };
-        int64_t steps = 0;
-        for (int32_t sg = 0; sg < c->n_offseg; ++sg) steps += (pair_ptr[sg + 1] - pair_ptr[sg] + 3) / 4;
-        const int64_t groups = 256 * 16 * 4;
-        const int64_t cap = 4 * std::max<int64_t>(8, steps / (4 * groups));
-        c->unit_steps = steps;
-        // The pieces of segment sg, emit(t0, t1, window): cut where the tile
-        // changes, but not into pieces of fewer than kMinRun couples (four
-        // steps; a piece costs a start, a reduction and 1,300 bytes of partial
-        // block; 8 and 32 time alike), then by the cap.
-        constexpr int32_t kMinRun = 16;
-        auto pieces = [&](int32_t sg, auto&& emit) {
-            const int32_t a = pair_ptr[sg], b = pair_ptr[sg + 1];
-            int32_t lo = a;
-            while (lo < b) {
-                int32_t hi = b;
-                if (tiled && b - lo >= 2 * kMinRun)
-                    for (int32_t t = lo + kMinRun; t <= b - kMinRun; ++t)
-                        if (tile[rq[trip[2 * (size_t)t]]] != tile[rq[trip[2 * (size_t)t - 2]]]) { hi = t; break; }
-                const int32_t w = tiled ? tile[rq[trip[2 * (size_t)((lo + hi) / 2)]]] : clus[seg_row[sg]];
-                for (int64_t t = lo; t < hi; t += cap) emit((int32_t)t, (int32_t)std::min<int64_t>(t + cap, hi), w);
-                lo = hi;
-            }
-        };
-        std::vector<int32_t> n_piece(nseg);
-        parallel_for(nseg, 256, [&](int64_t s0, int64_t s1, int) {
-            for (int64_t sg = s0; sg < s1; ++sg) pieces((int32_t)sg, [&](int32_t, int32_t, int32_t) { ++n_piece[sg]; });
-        });
-        // first unit and first partial block of each segment; split segments
-        // of more than kLongSeg pieces come first in the list
-        std::vector<int32_t> u0(nseg), p0(nseg, -1);
-        int32_t n_p = 0, n_u = 0;
-        for (int32_t sg = 0; sg < nseg; ++sg) { u0[sg] = n_u; n_u += n_piece[sg]; }
+        // first partial block of each segment; split segments of more than
+        // kLongSeg pieces come first in the list
+        std::vector<int32_t> p0(nseg, -1);
+        int32_t n_p = 0;
         for (int pass = 0; pass < 2; ++pass) {
             for (int32_t sg = 0; sg < nseg; ++sg) {
                 if (n_piece[sg] < 2 || (n_piece[sg] > ba::kLongSeg) != (pass == 0)) continue;
@@ -532,25 +564,37 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
             }
             if (pass == 0) c->n_lseg_long = (int32_t)lseg_blk.size();
         }
-        std::vector<Unit> units(n_u);
-        parallel_for(nseg, 256, [&](int64_t s0, int64_t s1, int) {
-            for (int64_t sg = s0; sg < s1; ++sg) {
-                int32_t i = 0;
-                pieces((int32_t)sg, [&](int32_t t0, int32_t t1, int32_t w) {
-                    units[u0[sg] + i] = {w, t0, t1, p0[sg] < 0 ? off_blk[sg] : -(p0[sg] + i + 1)};
-                    ++i;
-                });
+        std::vector<int32_t> u0(nr + 1, 0);   // first unit of each row
+        for (int32_t r = 0; r < nr; ++r) u0[r + 1] = u0[r] + (int32_t)piece[r].size();
+        const int32_t nu = u0[nr];
+        std::vector<Unit> made(nu), units(nu);
+        parallel_for(nr, 64, [&](int64_t r0, int64_t r1, int) {
+            for (int64_t r = r0; r < r1; ++r) {
+                const Piece* P = piece[r].data();
+                int32_t u = u0[r];
+                for (int32_t sg = sptr[r]; sg < sptr[r + 1]; ++sg)
+                    for (int32_t i = 0; i < n_piece[sg]; ++i, ++P, ++u)
+                        made[u] = {P->win, P->t0, P->t1, p0[sg] < 0 ? off_blk[sg] : -(p0[sg] + i + 1)};
             }
         });
-        std::stable_sort(units.begin(), units.end(), [](const Unit& x, const Unit& y) {
-            return x.win != y.win ? x.win < y.win : x.t1 - x.t0 > y.t1 - y.t0;
+        // by window, longest first, then in order of the segments
+        std::vector<int64_t> win_ptr;
+        std::vector<int32_t> by_win;
+        counting_sort(nu, n_cl, [&](int64_t u) { return made[u].win; }, win_ptr, by_win);
+        unit_rng.resize(2 * (size_t)nu);
+        unit_dst.resize(nu);
+        parallel_for(n_cl, 16, [&](int64_t w0, int64_t w1, int) {
+            for (int64_t w = w0; w < w1; ++w)
+                std::stable_sort(by_win.begin() + win_ptr[w], by_win.begin() + win_ptr[w + 1], [&](int32_t x, int32_t y) {
+                    return made[x].t1 - made[x].t0 > made[y].t1 - made[y].t0;
+                });
+            for (int64_t k = win_ptr[w0]; k < win_ptr[w1]; ++k) {
+                const Unit& u = units[k] = made[by_win[k]];
+                unit_rng[2 * k] = u.t0;
+                unit_rng[2 * k + 1] = u.t1;
+                unit_dst[k] = u.dst;
+            }
         });
-        const int32_t nu = (int32_t)units.size();
-        for (const Unit& u : units) {
-            unit_rng.push_back(u.t0);
-            unit_rng.push_back(u.t1);
-            unit_dst.push_back(u.dst);
-        }
         // XCD ranges of equal work: a wave costs its longest unit's steps plus one
         const int32_t nw = (nu + 3) / 4;
         std::vector<int64_t> cum(nw + 1, 0);
