@@ -51,6 +51,10 @@ void dalloc(ba_ctx* c, T** p, size_t n) {
     c->bytes += bytes;
 }
 
+// Bytes of the copy of both triangles of S above which AUTO takes the UPPER
+// product with any preconditioner (select_solver_matrix)
+constexpr double kFullMax = 256.0 * (1 << 20);
+
 template <typename T>
 void upload(ba_ctx* c, T** p, const std::vector<T>& h) {
     dalloc(c, p, h.size());
@@ -748,7 +752,9 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     dalloc(c, &c->ebar, (size_t)(shared ? n : rowobs_ptr[nr]) * 2);
     dalloc(c, &c->pblk, (size_t)c->n_pblk * 81);
     dalloc(c, &c->blk, (size_t)c->n_blk * 81);
-    dalloc(c, &c->Sf, (size_t)c->n_sf * 81);
+    // (a larger copy of both triangles, which AUTO does not use, on first use; the
+    // memory of a cap is taken here)
+    if (c->cap || (double)c->n_sf * 81 * sizeof(double) <= kFullMax) dalloc(c, &c->Sf, (size_t)c->n_sf * 81);
     dalloc(c, &c->rhs, (size_t)nr * 9);
     dalloc(c, &c->Minv, (size_t)nr * 81);
     dalloc(c, &c->Linv, (size_t)nr * 81);
@@ -888,7 +894,7 @@ ba_status form_rcs_async(ba_ctx* c, double lambda, bool point_done, int end) {
 size_t n_params(const ba_ctx* c) { return 6 * (size_t)c->n_cams + 5 * (size_t)c->n_phys; }
 
 // selects the S copy and the product layout of the next solve (allocating
-// the FP32 copies on first use).  AUTO: FULL needs one kernel less an
+// the copies that creation left out on first use).  AUTO: FULL needs one kernel less an
 // iteration, UPPER reads each block once; with a block-diagonal M they break
 // even near 128 MiB of FULL copy (FP64, us an iteration FULL / UPPER: 92 MiB
 // 29.7 / 29.5, 136 MiB 36.4 / 34.0, 242 MiB 54.6 / 44.4; FP32: 121 MiB 37.0 /
@@ -896,17 +902,22 @@ size_t n_params(const ba_ctx* c) { return 6 * (size_t)c->n_cams + 5 * (size_t)c-
 // by the layout too (UPPER in FP16) and keeps the limit of 256 MiB.
 void select_solver_matrix(ba_ctx* c, int fp32, int product, bool factorised) {
     c->s32 = fp32 ? 1 : 0;
-    const double full_bytes = (double)c->n_sf * 81 * (c->s32 ? sizeof(float) : sizeof(double)), MiB = 1 << 20;
-    const bool large = full_bytes > 256.0 * MiB;
+    const double full_bytes = (double)c->n_sf * 81 * (c->s32 ? sizeof(float) : sizeof(double));
+    const bool large = full_bytes > kFullMax;
     c->upper = (product == BA_PRODUCT_UPPER ||
-                (product == BA_PRODUCT_AUTO && (large || (!factorised && full_bytes > 128.0 * MiB)))) ? 1 : 0;
-    if (c->s32 && !c->Sf32) dalloc(c, &c->Sf32, (size_t)std::max<int64_t>(c->n_sf, 1) * 81);
+                (product == BA_PRODUCT_AUTO && (large || (!factorised && full_bytes > 0.5 * kFullMax)))) ? 1 : 0;
+    auto full_copy = [&]() {
+        if (c->s32 && !c->Sf32) dalloc(c, &c->Sf32, (size_t)std::max<int64_t>(c->n_sf, 1) * 81);
+        if (!c->s32 && !c->Sf) dalloc(c, &c->Sf, (size_t)c->n_sf * 81);
+    };
+    if (!c->upper || c->cap) full_copy();   // (under a cap in any layout, so that it decides alike)
     if (c->upper && c->s32 && !c->Su32) {
         try {
             dalloc(c, &c->Su32, (size_t)c->n_blk * 81);
         } catch (const ba_oom&) {
             if (product != BA_PRODUCT_AUTO || large) throw;
             c->upper = 0;   // between the limits FULL does, and needs no second copy
+            full_copy();
         }
     }
 }

@@ -1,7 +1,7 @@
-"""Contexts under a workspace cap (needs a GPU): caps that held a context
-before it had plans for solves in one kernel still hold it, and a cap that
-held the FULL layout's FP32 copy of S still holds a solve that may choose its
-layout."""
+"""Device memory of contexts (needs a GPU): caps that held a context before it
+had plans for solves in one kernel still hold it, a cap that held the FULL
+layout's FP32 copy of S still holds a solve that may choose its layout, and
+without a cap a large copy of both triangles waits for its first use."""
 import numpy as np
 import pytest
 
@@ -54,6 +54,8 @@ def test_fp32_solve_of_a_mid_sized_system():
             assert 128 << 20 < (2 * sz["n_blk"] - sz["n_rows"]) * 81 * 4 <= 256 << 20
             x = torch.zeros((sz["n_rows"], 9), dtype=torch.float64, device="cuda")
             kw = dict(tol=1e-8, max_iter=20, solver_fp32=True)
+            if not cap:   # both copies of FULL, which a capped context has room for from its start
+                ba.ba_pcg_solve(ctx, x, tol=1e-8, max_iter=2, product=ba.BA_PRODUCT_FULL)
             ba.ba_pcg_solve(ctx, x, product=ba.BA_PRODUCT_AUTO if cap else ba.BA_PRODUCT_FULL, **kw)
             out.append(x.clone())
             bytes_full = ba.ba_get_sizes(ctx)["device_bytes"]
@@ -66,3 +68,34 @@ def test_fp32_solve_of_a_mid_sized_system():
         finally:
             ba.ba_destroy(ctx)
     assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
+
+
+def test_large_copy_on_first_use():
+    """FULL copy above 256 MiB: AUTO solves with UPPER.  The context holds the
+    copy only once FULL is asked for, with the same result as under a cap,
+    which the copy is held against from the start."""
+    s = scenegen.aerial_grid_scene(seed=5, nx=125, ny=120, n_pts=300_000, with_stats=False)
+    args = (s.n_cams, s.n_pts, s.obs_cam, s.obs_pt, orc.observations(s))
+    held, out = [], []
+    for cap in (0, 64 << 30):
+        ctx = _create(*args, cap=cap)
+        try:
+            ba.ba_linearize(ctx, T(s.cams_init, torch.float64), T(s.pts_init, torch.float64))
+            ba.ba_form_rcs(ctx, 1e-2)
+            sz = ba.ba_get_sizes(ctx)
+            copy = (2 * sz["n_blk"] - sz["n_rows"]) * 81 * 8
+            assert copy > 256 << 20
+            held.append([sz["device_bytes"]])
+            x = torch.zeros((sz["n_rows"], 9), dtype=torch.float64, device="cuda")
+            for product in (ba.BA_PRODUCT_AUTO, ba.BA_PRODUCT_FULL, ba.BA_PRODUCT_UPPER, ba.BA_PRODUCT_FULL):
+                ba.ba_pcg_solve(ctx, x, tol=1e-8, max_iter=20, product=product)
+                out.append(x.clone())
+                held[-1].append(ba.ba_get_sizes(ctx)["device_bytes"])
+        finally:
+            ba.ba_destroy(ctx)
+    free, capped = held
+    assert free == [free[0], free[0], free[0] + copy, free[0] + copy, free[0] + copy]
+    assert capped == [free[0] + copy] * 5
+    for a, b in zip(out[:4], out[4:]):
+        assert torch.equal(a, b)
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
