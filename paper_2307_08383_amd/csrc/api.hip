@@ -572,7 +572,10 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         for (int32_t r = 0; r < nr; ++r) u0[r + 1] = u0[r] + (int32_t)piece[r].size();
         const int32_t nu = u0[nr];
         std::vector<Unit> made(nu), units(nu);
-        parallel_for(nr, 64, [&](int64_t r0, int64_t r1, int) {
+        // rows and windows of some 16,000 units a piece of work: a thread takes longer
+        // to start than that
+        auto grain = [&](int64_t n) { return std::max<int64_t>(1, n * (1 << 14) / std::max(nu, 1)); };
+        parallel_for(nr, grain(nr), [&](int64_t r0, int64_t r1, int) {
             for (int64_t r = r0; r < r1; ++r) {
                 const Piece* P = piece[r].data();
                 int32_t u = u0[r];
@@ -587,16 +590,15 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
         counting_sort(nu, n_cl, [&](int64_t u) { return made[u].win; }, win_ptr, by_win);
         unit_rng.resize(2 * (size_t)nu);
         unit_dst.resize(nu);
-        parallel_for(n_cl, 16, [&](int64_t w0, int64_t w1, int) {
+        parallel_for(n_cl, grain(n_cl), [&](int64_t w0, int64_t w1, int) {
+            for (int64_t k = win_ptr[w0]; k < win_ptr[w1]; ++k) units[k] = made[by_win[k]];
             for (int64_t w = w0; w < w1; ++w)
-                std::stable_sort(by_win.begin() + win_ptr[w], by_win.begin() + win_ptr[w + 1], [&](int32_t x, int32_t y) {
-                    return made[x].t1 - made[x].t0 > made[y].t1 - made[y].t0;
-                });
+                std::stable_sort(units.begin() + win_ptr[w], units.begin() + win_ptr[w + 1],
+                                 [](const Unit& x, const Unit& y) { return x.t1 - x.t0 > y.t1 - y.t0; });
             for (int64_t k = win_ptr[w0]; k < win_ptr[w1]; ++k) {
-                const Unit& u = units[k] = made[by_win[k]];
-                unit_rng[2 * k] = u.t0;
-                unit_rng[2 * k + 1] = u.t1;
-                unit_dst[k] = u.dst;
+                unit_rng[2 * k] = units[k].t0;
+                unit_rng[2 * k + 1] = units[k].t1;
+                unit_dst[k] = units[k].dst;
             }
         });
         // XCD ranges of equal work: a wave costs its longest unit's steps plus one
