@@ -200,7 +200,11 @@ typedef struct ba_pcg_info {
  * BA_ERR_NOT_CONVERGED (dxc still valid) or BA_ERR_NOT_SPD as warnings/errors;
  * BA_ERR_STATE without a formed RCS.  A learned preconditioner that fails
  * (d^T S d <= 0, or a non-finite residual) is replaced by block-Jacobi for
- * the same solve, reported in info->precond_fallback. */
+ * the same solve, reported in info->precond_fallback.
+ * A small system is solved by one kernel whose workgroups wait for each other.
+ * If they do not all run at once (another process's kernels hold the GPU) a
+ * wait gives up after a second or more; the solve is then repeated with one
+ * kernel per phase, as are the context's later ones: the same result, slower. */
 ba_status ba_pcg_solve(ba_ctx* ctx, const ba_pcg_opts* opts, double* dxc, ba_pcg_info* info_host);
 
 /* Sec. 6.2: y = S x with the RCS formed last, computed as one product of a

@@ -99,3 +99,26 @@ def test_large_copy_on_first_use():
     for a, b in zip(out[:4], out[4:]):
         assert torch.equal(a, b)
     assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+
+
+def test_no_tiles_under_a_cap():
+    """Above 4 GiB of records the pair stage works by tiles of points, whose
+    partial blocks a cap would count: under one, pairs stay whole.  The blocks
+    differ in the order of their sums alone (bits, but not by 1e-11 of the
+    largest entry), and the context holds no more than without tiles."""
+    s = scenegen.aerial_grid_scene(seed=13, nx=60, ny=50, n_pts=5_900_000, with_stats=False)
+    assert s.n_obs * 192 > 4 << 30
+    args = (s.n_cams, s.n_pts, s.obs_cam, s.obs_pt, orc.observations(s))
+    blk, held = [], []
+    for cap in (0, 64 << 30):
+        ctx = _create(*args, cap=cap)
+        try:
+            ba.ba_linearize(ctx, T(s.cams_init, torch.float64), T(s.pts_init, torch.float64))
+            ba.ba_form_rcs(ctx, 1e-2)
+            blk.append(ba.ba_get_rcs(ctx)[0])
+            held.append(ba.ba_get_sizes(ctx)["device_bytes"])
+        finally:
+            ba.ba_destroy(ctx)
+    assert not np.array_equal(*blk) and held[0] > held[1]
+    scale = np.abs(blk[0]).reshape(len(blk[0]), -1).max(1)
+    assert (np.abs(blk[0] - blk[1]).reshape(len(blk[0]), -1).max(1) <= 1e-11 * np.maximum(scale, scale.max() * 1e-6)).all()
