@@ -22,7 +22,7 @@
 // matrix does not change over the steps and is formed once; the undistortion
 // stops where Newton's quadratic convergence has reached the last bit (its
 // step never fell under 1e-17 of the radius, so it ran to its limit of 60).
-// 9.4M observations, linear start and 4 steps: 1,300 us before, 622 now.
+// 9.4M observations, linear start and 4 steps: 1,300 us before, 615 now.
 #include "ba_common.hpp"
 
 namespace ba {
@@ -65,22 +65,39 @@ __device__ __forceinline__ double undistort_radius(double rho, double k1, double
     return r;
 }
 
-// D = R(w) - I = a [w]x + b [w]x^2, row-major (the diagonal's w_i^2 - |w|^2 without
-// the difference, which would leave the rounding of |w|^2 in small entries)
-__device__ __forceinline__ void rotation(const double* w, double* D) {
-    const double s = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
+// R(w) = I + a [w]x + b [w]x^2 as diag(s) + D, row-major: s_i = 1 or -1, whichever
+// is next to R_ii, which leaves small entries of D that carry no rounding of
+// entries near 1: D_ii = -b (|w|^2 - w_i^2), or with 1 + cos|w| = a^2 / b (since
+// sin^2 = (1 - cos)(1 + cos)) D_ii = a^2 / b + b w_i^2
+struct Rot {
+    double D[9];
+    int neg;   // bit i: s_i = -1
+    __device__ __forceinline__ double s(int i, double v) const { return (neg >> i & 1) ? -v : v; }
+};
+__device__ __forceinline__ void rotation(const double* w, Rot& R) {
+    const double s2[3] = {w[0] * w[0], w[1] * w[1], w[2] * w[2]};
     double a, b, as, bs;
-    rot_coeffs(s, a, b, as, bs);
-    D[0] = -b * (w[1] * w[1] + w[2] * w[2]); D[1] = -a * w[2] + b * w[0] * w[1]; D[2] = a * w[1] + b * w[0] * w[2];
-    D[3] = a * w[2] + b * w[1] * w[0]; D[4] = -b * (w[0] * w[0] + w[2] * w[2]); D[5] = -a * w[0] + b * w[1] * w[2];
-    D[6] = -a * w[1] + b * w[2] * w[0]; D[7] = a * w[0] + b * w[2] * w[1]; D[8] = -b * (w[0] * w[0] + w[1] * w[1]);
+    rot_coeffs(s2[0] + s2[1] + s2[2], a, b, as, bs);
+    const double opc = a * a / b;
+    const double m[3] = {b * (s2[1] + s2[2]), b * (s2[0] + s2[2]), b * (s2[0] + s2[1])};
+    R.neg = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const bool neg = m[i] > 1.0;
+        R.neg |= (int)neg << i;
+        R.D[i * 4] = neg ? opc + b * s2[i] : -m[i];
+    }
+    R.D[1] = -a * w[2] + b * w[0] * w[1]; R.D[2] = a * w[1] + b * w[0] * w[2];
+    R.D[3] = a * w[2] + b * w[1] * w[0]; R.D[5] = -a * w[0] + b * w[1] * w[2];
+    R.D[6] = -a * w[1] + b * w[2] * w[0]; R.D[7] = a * w[0] + b * w[2] * w[1];
 }
 
-// The terms of observation (camera c with R = I + D, pixel ou, ov) in the normal equations
+// The terms of observation (camera c with rotation Q, pixel ou, ov) in the normal equations
 // of the linear multi-view solve: A^T A (6 unique) and A^T b of its two rows
 // (x R_3 - R_1) X = t_1 - x t_3, (y R_3 - R_2) X = t_2 - y t_3.
-__device__ __forceinline__ void tri_linear_terms(const double* c, const double* D, double ou, double ov, double* m) {
-    const double R[9] = {1.0 + D[0], D[1], D[2], D[3], 1.0 + D[4], D[5], D[6], D[7], 1.0 + D[8]};
+__device__ __forceinline__ void tri_linear_terms(const double* c, const Rot& Q, double ou, double ov, double* m) {
+    const double* D = Q.D;
+    const double R[9] = {Q.s(0, 1.0) + D[0], D[1], D[2], D[3], Q.s(1, 1.0) + D[4], D[5], D[6], D[7], Q.s(2, 1.0) + D[8]};
     const double rho = sqrt(ou * ou + ov * ov) / c[6];
     double x = 0.0, y = 0.0;
     if (rho > 0.0) {
@@ -104,16 +121,19 @@ __device__ __forceinline__ void tri_linear_terms(const double* c, const double* 
 
 // The terms of the Gauss-Newton step on the point's reprojection error at X:
 // J_p^T J_p (6 unique) and -J_p^T e (the projection and J_p of project_point,
-// with D = R - I given).  The point is turned by (X + t) + D X: along the axis D
-// is small, where R X rounds at the size of X before the translation takes most
-// of it away.  9.4M observations of points up to 900 units from the origin, error
-// against 64 bits relative to the points' norm: 8.2e-16 by R X (615 us), 4.3e-16
-// by X + a w x X + b w x (w x X) + t (686), 3.4e-16 so (622).
-__device__ __forceinline__ void tri_gn_terms(const double* c, const double* D, const double* X, double ou, double ov,
+// with the rotation given).  The point is turned by (s X + t) + D X, whose
+// first sum is exact or nearly so: R X rounds at the size of X before the
+// translation takes most of it away.  Error against 64 bits relative to the
+// points' norm, 9.4M observations of strips 900 units long and of a 100 x 100
+// block: R X 8.3e-16 and 5.1e-16 (605 us the strips), the projection's
+// X + a w x X + b w x (w x X) + t 4.3e-16 and 5.2e-16 (673), (X + t) + (R - I) X
+// 3.4e-16 and 5.6e-16 (612), this 3.4e-16 and 4.4e-16 (614).
+__device__ __forceinline__ void tri_gn_terms(const double* c, const Rot& Q, const double* X, double ou, double ov,
                                              double* m) {
-    const double P0 = (X[0] + c[3]) + D[0] * X[0] + D[1] * X[1] + D[2] * X[2];
-    const double P1 = (X[1] + c[4]) + D[3] * X[0] + D[4] * X[1] + D[5] * X[2];
-    const double P2 = (X[2] + c[5]) + D[6] * X[0] + D[7] * X[1] + D[8] * X[2];
+    const double* D = Q.D;
+    const double P0 = (Q.s(0, X[0]) + c[3]) + D[0] * X[0] + D[1] * X[1] + D[2] * X[2];
+    const double P1 = (Q.s(1, X[1]) + c[4]) + D[3] * X[0] + D[4] * X[1] + D[5] * X[2];
+    const double P2 = (Q.s(2, X[2]) + c[5]) + D[6] * X[0] + D[7] * X[1] + D[8] * X[2];
     const double iz = 1.0 / P2;
     const double x = P0 * iz, y = P1 * iz;
     const double r2 = x * x + y * y;
@@ -124,11 +144,12 @@ __device__ __forceinline__ void tri_gn_terms(const double* c, const double* D, c
     const double A00 = f * (d + 2.0 * x * x * dd), A01 = f * (2.0 * x * y * dd), A11 = f * (d + 2.0 * y * y * dd);
     const double E00 = A00 * iz, E01 = A01 * iz, E02 = -(A00 * x + A01 * y) * iz;
     const double E10 = A01 * iz, E11 = A11 * iz, E12 = -(A01 * x + A11 * y) * iz;
-    double jp[6] = {E00, E01, E02, E10, E11, E12};   // E (I + D)
+    const double R[9] = {Q.s(0, 1.0) + D[0], D[1], D[2], D[3], Q.s(1, 1.0) + D[4], D[5], D[6], D[7], Q.s(2, 1.0) + D[8]};
+    double jp[6];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-        jp[j] = jp[j] + E00 * D[j] + E01 * D[3 + j] + E02 * D[6 + j];
-        jp[3 + j] = jp[3 + j] + E10 * D[j] + E11 * D[3 + j] + E12 * D[6 + j];
+        jp[j] = E00 * R[j] + E01 * R[3 + j] + E02 * R[6 + j];
+        jp[3 + j] = E10 * R[j] + E11 * R[3 + j] + E12 * R[6 + j];
     }
     m[0] = jp[0] * jp[0] + jp[3] * jp[3];
     m[1] = jp[0] * jp[1] + jp[3] * jp[4];
@@ -141,9 +162,11 @@ __device__ __forceinline__ void tri_gn_terms(const double* c, const double* D, c
     m[8] = -(jp[2] * eu + jp[5] * ev);
 }
 
-// One wave per workgroup: its barriers hold a single wave.
+// One wave per workgroup: its barriers hold a single wave.  Five waves a SIMD
+// asked for: at 100 registers, four without, it took 671 us instead of 621 (two
+// spilled) in an earlier form of the terms.
 template <bool LINEAR>
-__global__ __launch_bounds__(kWave) void k_triangulate(int n_chunk, const int32_t* __restrict__ chunk_ptr, int n,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(5))) void k_triangulate(int n_chunk, const int32_t* __restrict__ chunk_ptr, int n,
                                                        const int32_t* __restrict__ obs_cam,
                                                        const int32_t* __restrict__ obs_pt,
                                                        const int32_t* __restrict__ obs_row,
@@ -160,7 +183,8 @@ __global__ __launch_bounds__(kWave) void k_triangulate(int n_chunk, const int32_
     const int p = act ? obs_pt[k] : -1;
     const Track tk = chunk_track(act, p, lane, k1 - k0);
     const int head = tk.head, tl = tk.len;
-    double c[9], D[9], X[3];
+    double c[9], X[3];
+    Rot Q;
     double ou = 0.0, ov = 0.0;
     bool ok = true;   // the same in every lane of a track
     if (act) {
@@ -168,7 +192,7 @@ __global__ __launch_bounds__(kWave) void k_triangulate(int n_chunk, const int32_
         const int row = obs_row[k];
 #pragma unroll
         for (int i = 0; i < 9; ++i) c[i] = c0[i] + ((dxc && row >= 0) ? dxc[(int64_t)row * 9 + i] : 0.0);
-        rotation(c, D);
+        rotation(c, Q);
         ou = uv[k];
         ov = uv[n + k];
         // start: the point as given (out may be pts: the track's lanes all
@@ -179,8 +203,8 @@ __global__ __launch_bounds__(kWave) void k_triangulate(int n_chunk, const int32_
     for (int it = LINEAR ? -1 : 0; it < n_gn; ++it) {
         if (act) {
             double m[9];
-            if (LINEAR && it < 0) tri_linear_terms(c, D, ou, ov, m);
-            else tri_gn_terms(c, D, X, ou, ov, m);
+            if (LINEAR && it < 0) tri_linear_terms(c, Q, ou, ov, m);
+            else tri_gn_terms(c, Q, X, ou, ov, m);
 #pragma unroll
             for (int j = 0; j < 9; ++j) sA[j][lane] = m[j];
         }
@@ -264,11 +288,12 @@ __global__ __launch_bounds__(BS) void k_triangulate_long(const int32_t* __restri
         for (int m = 0; m < 9; ++m) v[m] = 0.0;
         const double X[3] = {sX[0], sX[1], sX[2]};
         for (int k = k0 + threadIdx.x; k < k1; k += BS) {
-            double c[9], D[9], t[9];
+            double c[9], t[9];
+            Rot Q;
             camera(k, c);
-            rotation(c, D);
-            if (it < 0) tri_linear_terms(c, D, uv[k], uv[n + k], t);
-            else tri_gn_terms(c, D, X, uv[k], uv[n + k], t);
+            rotation(c, Q);
+            if (it < 0) tri_linear_terms(c, Q, uv[k], uv[n + k], t);
+            else tri_gn_terms(c, Q, X, uv[k], uv[n + k], t);
 #pragma unroll
             for (int m = 0; m < 9; ++m) v[m] += t[m];
         }

@@ -55,12 +55,14 @@ def gauss_newton(s, uv, n, dtype):
     return X
 
 
-def test_error_far_from_the_origin():
+@pytest.mark.parametrize("nx,ny", [(900, 3), (60, 50)])
+def test_error_far_from_the_origin(nx, ny):
     """The library's error is that of the same formula in FP64 numpy but for
     the contraction of products and sums: the median over the points of the
     largest component's error within 1.5 times numpy's.  (Turned by R X, which
-    rounds at the size of X, it would be 2 to 3 times as large.)"""
-    s = scenegen.aerial_grid_scene(seed=21, nx=900, ny=3, n_pts=12_000, with_stats=False)
+    rounds at the size of X, it would be 2 to 3 times as large in the line of
+    cameras.)"""
+    s = scenegen.aerial_grid_scene(seed=21, nx=nx, ny=ny, n_pts=12_000, with_stats=False)
     uv = orc.observations(s)
     near = np.ones(s.n_pts, bool)   # points of a narrow view, whose steps converge
     np.logical_and.at(near, s.obs_pt, np.linalg.norm(uv, axis=0) / s.cams_init[s.obs_cam, 6] < 1.0)
