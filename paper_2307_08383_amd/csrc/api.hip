@@ -804,7 +804,7 @@ void build(ba_ctx* c, const std::vector<int32_t>& cam, const std::vector<int32_t
     for (auto& e : c->ev) BA_HIP_CHECK(hipEventCreate(&e));
     BA_HIP_CHECK(hipStreamCreateWithFlags(&c->capture_stream, hipStreamNonBlocking));
     if (const char* g = std::getenv("BA_PCG_GRAPHS")) c->use_graphs = std::atoi(g) != 0;
-    if (const char* g = std::getenv("BA_CHIP_POLLS")) c->chip_polls = std::max(-1, std::atoi(g));
+    if (const char* g = std::getenv("BA_CHIP_GIVE_UP")) c->chip_give_up = std::atoi(g);
     ph.mark("workspace");
     // point ids and pixels in the internal order, gathered on the device
     // (the permutation travels in the record buffer, written only later)

@@ -18,7 +18,6 @@ namespace ba {
 constexpr int kWave = 64;          // CDNA wavefront width
 constexpr int kMaxTrack = 64;      // observations per point handled by one wave (longer tracks: one workgroup)
 constexpr int kPcgBatch = 16;      // PCG iterations per enqueued batch (one graph)
-constexpr int kChipPolls = 1 << 21;   // polls before a wait of the solve in one kernel gives up (over a second)
 constexpr int kLongSeg = 24;       // chunks of a split pair segment summed by one thread per entry
 constexpr int kRec = 24;           // per-observation record: J_c (18), then K = J_p L^-T (6)
 
@@ -589,9 +588,11 @@ struct ba_ctx {
     ba::Fsai fs;
     ba::Csr csr;
     ba::Chip chip, chip_ord;
-    // BA_CHIP_POLLS from the environment at creation (tests of the recovery): the
-    // limit of a wait, 0: give up at the first one, -1: report it at the end
-    int chip_polls = ba::kChipPolls;
+    // BA_CHIP_GIVE_UP from the environment at creation (tests of the recovery): 1:
+    // the launch of a solve in one kernel counts as refused, 2: a workgroup is
+    // reported to have given up when all have written their results.  (Not in the
+    // kernel: 12 bytes more before its loop cost 1.5% of an iteration.)
+    int chip_give_up = 0;
     hipEvent_t ev[2] = {};             // the two batches of iterations in flight
     // Time stamps of the stages (100 MHz clock), written to pinned memory by
     // the stages' own kernels: an event in the stream between two kernels held

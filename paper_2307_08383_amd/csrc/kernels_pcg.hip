@@ -618,6 +618,8 @@ __global__ __launch_bounds__(BS) void k_pcg_init(int n_rows, const double* __res
     if (blockIdx.x == 0 && threadIdx.x == 0) { state[0] = 0; state[1] = 0; state[2] = BA_OK; state[3] = 0; state[4] = 0; scal[1] = -1.0; }
 }
 
+__global__ void k_give_up(int* state) { state[4] = 1; }
+
 __global__ void k_report(const int* __restrict__ state, const double* __restrict__ scal, int* __restrict__ h_state,
                          double* __restrict__ h_scal, u64* stamp) {
     stamp_now(stamp);
@@ -1385,8 +1387,9 @@ ba_status run_pcg(ba_ctx* c, int mode, const double* M, int defl, double tol, in
         // gives up, whose workgroups write what they have
         const int64_t n = (int64_t)nr * 9;
         double* const to = x0 && x0 < out + n && out < x0 + n ? P.x : out;
-        const bool launched = ordered ? launch_chip_ordered(c, M, g, tol, max_iter, to)
-                                      : launch_chip(c, mode, M, defl, g, tol, max_iter, to);
+        const bool launched = c->chip_give_up != 1 && (ordered ? launch_chip_ordered(c, M, g, tol, max_iter, to)
+                                                               : launch_chip(c, mode, M, defl, g, tol, max_iter, to));
+        if (launched && c->chip_give_up == 2) k_give_up<<<1, 1, 0, st>>>(P.state);
         if (launched && !wait) {
             *iters = -1;
             return BA_OK;

@@ -36,9 +36,9 @@
 // sum with one copy, 2.7 with 4 or 8).
 //
 // All workgroups are resident at once (cooperative launch, at most one per
-// CU).  Every wait is bounded all the same: a workgroup that polls too often
-// (ba_ctx::chip_polls) reports it in state[4] and returns, so do the others, and
-// the host solves with the kernels of kernels_pcg.hip.
+// CU).  Every wait is bounded all the same: a workgroup that waits too long
+// reports it in state[4] and returns, so do the others, and the host solves
+// with the kernels of kernels_pcg.hip.
 #include <algorithm>
 
 #include "ba_common.hpp"
@@ -58,11 +58,10 @@ constexpr int kMaxG = 256;             // workgroups (one per CU)
 constexpr int kRep = 4;                // replicas of a sum's words
 constexpr int NP = 9;                  // values of a partial (kernels_pcg.hip)
 constexpr int kW = 7;
+constexpr int kSpin = 1 << 21;         // polls before a wait gives up (over a second)
 
 struct ChipArgs {
     int max_iter, n_part, s32;
-    int polls;   // before a wait gives up; 0: every workgroup gives up at its first wait
-    int late;    // 1: the first workgroup reports after its last iteration that it gave up
     double tol;
     const int32_t *brow, *cptr, *cols;                 // plan (ba::Chip)
     const int32_t *sf_ptr, *sf_col, *sf_src;           // rows of both triangles
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
     for (int u = tid; u < kGrp * NB; u += BS) slc[u] = 0;
     if (tid < NV * NW) sh[tid] = 0.0;
     if (tid < NV * 4) shw[tid] = 0.0;
-    if (tid == 0) s_bad = a.polls == 0;
+    if (tid == 0) s_bad = 0;
     // lane groups of the rows before row `lane` when a group takes up to q of
     // a row's entries (one wave: R <= 40)
     auto group_starts = [&](const int32_t* ptr, int q, int* out) {
@@ -341,7 +340,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
                     for (int i = 0; i < kAt; ++i)
                         ok = ok && (unsigned)(w[i][0] >> 32) == nsum && (unsigned)(w[i][1] >> 32) == nsum;
                     if (ok) break;
-                    if (++spin > a.polls) { s_bad = 1; break; }
+                    if (++spin > kSpin) { s_bad = 1; break; }
                 }
 #pragma unroll
                 for (int i = 0; i < kAt; ++i) {
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
 #pragma unroll
             for (int i = 0; i < kEx; ++i) ok = ok && (unsigned)(w[i][0] >> 32) == nvec && (unsigned)(w[i][1] >> 32) == nvec;
             if (ok) break;
-            if (++spin > a.polls) { s_bad = 1; break; }
+            if (++spin > kSpin) { s_bad = 1; break; }
         }
 #pragma unroll
         for (int i = 0; i < kEx; ++i) {
@@ -556,7 +555,7 @@ __global__ __launch_bounds__(BS) void k_pcg_chip(ChipArgs a) {
         if (!take(z, a.zlo, a.zhi)) { fine = false; break; }
         ++k;
     }
-    if (!fine || (a.late && wg == 0)) {
+    if (!fine) {
         if (tid == 0) a.state[4] = 1;
         return;
     }
@@ -595,7 +594,7 @@ __global__ __launch_bounds__(BS) void k_pcg_ord(int n_rows, ChipArgs a) {
     const int c0 = a.cptr[wg], nc = a.cptr[wg + 1] - c0;
     const int n_a = (n_rows + 3) / 4, n_b = (n_rows + kOrdB - 1) / kOrdB;   // partials of the two sums
     for (int u = tid; u < nc; u += BS) scol[u] = a.cols[c0 + u];
-    if (tid == 0) s_bad = a.polls == 0;
+    if (tid == 0) s_bad = 0;
     __syncthreads();
     const int grp = lane / 9, comp = lane % 9;
     const bool live = row < n_rows, own = live && lane < 9;
@@ -660,7 +659,7 @@ __global__ __launch_bounds__(BS) void k_pcg_ord(int n_rows, ChipArgs a) {
             if ((unsigned)(w[0] >> 32) == ep && (unsigned)(w[1] >> 32) == ep && (unsigned)(w[2] >> 32) == ep &&
                 (unsigned)(w[3] >> 32) == ep)
                 return;
-            if (++spin > a.polls) { s_bad = 1; return; }
+            if (++spin > kSpin) { s_bad = 1; return; }
         }
     };
     const int myrep = wg % kRep;
@@ -816,7 +815,7 @@ __global__ __launch_bounds__(BS) void k_pcg_ord(int n_rows, ChipArgs a) {
         if (s_bad) { fine = false; break; }
         ++k;
     }
-    if (!fine || (a.late && wg == 0)) {
+    if (!fine) {
         if (tid == 0) a.state[4] = 1;
         return;
     }
@@ -914,7 +913,7 @@ bool launch_chip(ba_ctx* c, int mode, const double* M, int defl, int n_part, dou
     const Pcg& P = c->pcg;
     const Fsai& F = c->fs;
     ChipArgs a{};
-    a.max_iter = max_iter; a.polls = c->chip_polls < 0 ? kChipPolls : c->chip_polls; a.late = c->chip_polls < 0; a.n_part = n_part; a.s32 = c->s32; a.tol = tol;
+    a.max_iter = max_iter; a.n_part = n_part; a.s32 = c->s32; a.tol = tol;
     a.brow = H.brow; a.cptr = H.cptr; a.cols = H.cols;
     a.sf_ptr = c->sf_ptr; a.sf_col = c->sf_col; a.sf_src = c->sf_src;
     a.blk = c->blk; a.M = M;
@@ -966,7 +965,7 @@ bool launch_chip_ordered(ba_ctx* c, const double* M, int n_part, double tol, int
     const Chip& H = c->chip_ord;
     const Pcg& P = c->pcg;
     ChipArgs a{};
-    a.max_iter = max_iter; a.polls = c->chip_polls < 0 ? kChipPolls : c->chip_polls; a.late = c->chip_polls < 0; a.n_part = n_part; a.s32 = c->s32; a.tol = tol;
+    a.max_iter = max_iter; a.n_part = n_part; a.s32 = c->s32; a.tol = tol;
     a.cptr = H.cptr; a.cols = H.cols;
     a.sf_ptr = c->sf_ptr; a.sf_col = c->sf_col; a.sf_src = c->sf_src;
     a.blk = c->blk; a.M = M;

@@ -1,10 +1,10 @@
 """The PCG solves in one kernel against the kernels that run one phase each
-(needs a GPU): a solve whose waits give up is repeated with those, as if it
-had not been tried, and the solve that keeps their order of sums gives their
-result bit for bit.  BA_CHIP_POLLS, read at creation, sets how often a wait
-polls: 0 makes every workgroup give up at its first wait, -1 makes one report
-it at its end, when the others have written their results.  Either way every
-kernel ends normally, and the context solves with one kernel per phase
+(needs a GPU): a solve that could not be launched, or one of whose workgroups
+gave up waiting, is repeated with those as if it had not been tried, and the
+solve that keeps their order of sums gives their result bit for bit.
+BA_CHIP_GIVE_UP, read at creation: 1 takes the launch as refused, 2 takes one
+workgroup to have given up when all have written their results.  Either way
+the kernels end normally, and the context solves with one kernel per phase
 afterwards, which is the reference here."""
 import numpy as np
 import pytest
@@ -32,11 +32,11 @@ FORMS = {
 }
 
 
-def _context(monkeypatch, scene, polls=None):
-    if polls is None:
-        monkeypatch.delenv("BA_CHIP_POLLS", raising=False)
+def _context(monkeypatch, scene, give_up=None):
+    if give_up is None:
+        monkeypatch.delenv("BA_CHIP_GIVE_UP", raising=False)
     else:
-        monkeypatch.setenv("BA_CHIP_POLLS", str(polls))
+        monkeypatch.setenv("BA_CHIP_GIVE_UP", str(give_up))
     return create(scene, orc.observations(scene), 0)
 
 
@@ -51,15 +51,15 @@ def _solve(ctx, x, **kw):
     return (i["iters"], i["status"], i["relres"])
 
 
-@pytest.mark.parametrize("polls", [0, -1])
+@pytest.mark.parametrize("give_up", [1, 2])
 @pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name", ["tiny", "300"])
-def test_solve_given_up(monkeypatch, name, form, polls):
+def test_solve_given_up(monkeypatch, name, form, give_up):
     """The first solve gives up and is repeated, the second knows better: the
     same bits, without a start and with one that the result replaces."""
     s = SCENES[name]()
     for guess in (False, True):
-        ctx = _context(monkeypatch, s, polls)
+        ctx = _context(monkeypatch, s, give_up)
         try:
             n = _form(ctx, s)
             g = np.random.default_rng(7).standard_normal((n, 9)) * 1e-3
@@ -72,17 +72,17 @@ def test_solve_given_up(monkeypatch, name, form, polls):
         assert torch.equal(x, y)
 
 
-@pytest.mark.parametrize("polls", [0, -1])
+@pytest.mark.parametrize("give_up", [1, 2])
 @pytest.mark.parametrize("opts", [dict(pcg_tol=1e-10), dict(), dict(pcg_tol=1e-10, deflate=True),
                                   dict(pcg_tol=1e-10, precond=ba.BA_PRECOND_FSAI), dict(pcg_tol=1e-10, retriangulate=2)])
-def test_step_given_up(monkeypatch, opts, polls):
+def test_step_given_up(monkeypatch, opts, give_up):
     """A step whose solve gives up takes the step of the repeated solve, once:
     the parameters, the state and the report are those of a context that
     solves with one kernel per phase from the start; so is the next step."""
     s = SCENES["300"]()
     got = []
     for warned in (False, True):
-        ctx = _context(monkeypatch, s, polls)
+        ctx = _context(monkeypatch, s, give_up)
         try:
             if warned:   # a solve that gives up beforehand
                 n = _form(ctx, s)
@@ -107,11 +107,11 @@ def test_ordered_solve_bit_for_bit(monkeypatch, name, fp32):
     iterates, count and residual."""
     s = ordered.SCENES[name]()
     got = []
-    for polls in (None, 0):
-        ctx = _context(monkeypatch, s, polls)
+    for give_up in (None, 1):
+        ctx = _context(monkeypatch, s, give_up)
         try:
             n = _form(ctx, s)
-            if polls == 0:
+            if give_up == 1:
                 _solve(ctx, torch.zeros((n, 9), dtype=torch.float64, device="cuda"), tol=1e-6)
             res = []
             for kw in (dict(tol=1e-6, max_iter=3000), dict(tol=1e-7, max_iter=8), dict(tol=1e-7, max_iter=1)):
@@ -135,8 +135,8 @@ def test_iterates_of_the_tight_solve(monkeypatch, name, form):
     from no start and from one."""
     s = SCENES[name]()
     got = []
-    for polls in (None, 0):
-        ctx = _context(monkeypatch, s, polls)
+    for give_up in (None, 1):
+        ctx = _context(monkeypatch, s, give_up)
         try:
             n = _form(ctx, s)
             g = T(np.random.default_rng(7).standard_normal((n, 9)) * 1e-3, torch.float64)
